@@ -225,7 +225,9 @@ int lbm_init(lbm_ctx* ctx, int level, const double* rho, const double* u,
              const double* pi_neq, const uint8_t* mask);
 
 /* Enqueue n coarse steps (level l + 1 takes two steps per step of level l
- * on a refined context; n <= 1 with LBM_HALO faces, else LBM_EINVAL).
+ * on a refined context; n <= 1 with LBM_HALO faces, else LBM_EINVAL).  Where
+ * it is faster, two steps are taken in one pass over the grid; results do not
+ * depend on it (bitwise) nor on how n is split over calls.
  * Returns after enqueueing.  Kernel-side instability is recorded in a sticky
  * flag reported by lbm_sync / lbm_moments. */
 int lbm_step(lbm_ctx* ctx, int64_t n);

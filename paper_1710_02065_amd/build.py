@@ -1,7 +1,9 @@
 """Build the HIP library liblbm_hip.so for gfx950 (in-tree).
 
 hipcc cross-compiles without a GPU.  All HIP sources are compiled with packed
-FP32 instructions disabled.
+FP32 instructions disabled, and with multiply-adds contracted within one
+source expression only, so that a function rounds the same in every kernel
+that inlines it (the sweeps that share the collision give the same bits).
 """
 import os
 import shutil
@@ -12,12 +14,12 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbm_hip.so")
-SOURCES = ["kernels.hip", "msweep.hip", "runtime.hip", "refine.hip", "serve.hip"]
+SOURCES = ["kernels.hip", "pair3d.hip", "msweep.hip", "runtime.hip", "refine.hip", "serve.hip"]
 ARCH = os.environ.get("HRLBM_ARCH", "gfx950")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-std=c++17", "-O3", "--offload-arch=" + ARCH, "-fPIC",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-ffp-contract=on",
          "-Wall", "-Wno-unused-function", "-I" + os.path.join(HERE, "..", "include")]
 
 

@@ -150,9 +150,9 @@ __device__ __forceinline__ void halo_pack(const SweepArgs<S>& a, uint32_t c, uin
     constexpr int vl = last_component<L>(L::dir(i));
     constexpr int r = halo_rank<L>(i);
     if constexpr (vl < 0) {
-      if (lo) a.hsend[0][(uint64_t)r * a.hplane + pc] = (T)post[i];
+      if (lo) a.hsend[0][(uint64_t)r * a.hplane + pc] = narrow<T>(post[i]);
     } else if constexpr (vl > 0) {
-      if (hi) a.hsend[1][(uint64_t)r * a.hplane + pc] = (T)post[i];
+      if (hi) a.hsend[1][(uint64_t)r * a.hplane + pc] = narrow<T>(post[i]);
     }
   });
 }
@@ -423,7 +423,7 @@ __device__ __forceinline__ void sweep_cell(const SweepArgs<S>& a, uint32_t c) {
   }
   static_for<0, Q>([&](auto I) {
     constexpr int i = decltype(I)::value;
-    store_pop_nt(a.dst + (uint64_t)i * P, (uint32_t)(P * sizeof(T)), c, (T)post[i]);
+    store_pop_nt(a.dst + (uint64_t)i * P, (uint32_t)(P * sizeof(T)), c, narrow<T>(post[i]));
   });
 }
 

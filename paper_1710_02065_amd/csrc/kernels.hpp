@@ -86,6 +86,16 @@ struct StoreF16S {
   static constexpr bool kShifted = true;
 };
 
+// Rounding of a rebuilt value to the storage type.  For binary16 the FP32
+// value is made opaque first: folded into the multiply before it (one mixed
+// instruction, one rounding) the result would depend on how each kernel is
+// compiled.
+template <class T, class R>
+__device__ __forceinline__ T narrow(R v) {
+  if constexpr (sizeof(T) == 2) asm("" : "+v"(v));
+  return (T)v;
+}
+
 // stored value -> deviation h = f - w rho0
 template <class S>
 __device__ __forceinline__ typename S::R decode(typename S::T v,
@@ -102,9 +112,9 @@ __device__ __forceinline__ typename S::T encode(typename S::R h,
                                                 typename S::R wrho0) {
   using T = typename S::T;
   if constexpr (S::kShifted)
-    return (T)h;
+    return narrow<T>(h);
   else
-    return (T)(h + wrho0);
+    return narrow<T>(h + wrho0);
 }
 
 // Element idx of the population array starting at `base`, addressed as a
@@ -122,27 +132,28 @@ __device__ __forceinline__ T load_pop_nt(const T* base, uint32_t idx) {
   return __builtin_nontemporal_load(reinterpret_cast<const T*>(
       reinterpret_cast<const char*>(base) + (uint32_t)(idx * (uint32_t)sizeof(T))));
 }
-// Non-temporal store of element idx of a population array through a raw
-// buffer resource (scalar base, 32-bit offset, stores past `bytes` are
-// dropped by the hardware).  The third resource word 0x00020000 is the
+// Store at byte offset `off` + `soff` (element idx) of a population array
+// through a raw buffer resource (scalar base, 32-bit lane and scalar offsets,
+// stores past `bytes` are dropped by the hardware), with the non-temporal hint
+// (kNt).  The third resource word 0x00020000 is the
 // gfx9-family untyped 32-bit data format.
-template <class T>
-__device__ __forceinline__ void store_pop_nt(T* base, uint32_t bytes, uint32_t idx, T v) {
+template <bool kNt, class T>
+__device__ __forceinline__ void store_at(T* base, uint32_t bytes, uint32_t off, uint32_t soff, T v) {
   __amdgpu_buffer_rsrc_t r =
       __builtin_amdgcn_make_buffer_rsrc(base, (short)0, (int)bytes, 0x00020000);
-  constexpr int kNonTemporal = 2;
-  const uint32_t off = idx * (uint32_t)sizeof(T);
+  constexpr int kAux = kNt ? 2 : 0;
   if constexpr (sizeof(T) == 8) {
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0,
-                                          kNonTemporal);
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, soff, kAux);
   }
   else if constexpr (sizeof(T) == 4)
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, off, 0,
-                                          kNonTemporal);
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, off, soff, kAux);
   else
-    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), r, off, 0,
-                                          kNonTemporal);
+    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), r, off, soff, kAux);
+}
+template <class T>
+__device__ __forceinline__ void store_pop_nt(T* base, uint32_t bytes, uint32_t idx, T v) {
+  store_at<true>(base, bytes, idx * (uint32_t)sizeof(T), 0u, v);
 }
 
 // ------------------------------------------------------------------------
@@ -312,78 +323,123 @@ __device__ __forceinline__ void static_for(F&& f) {
 // All q populations from the coefficients.  Directions come in opposite
 // pairs (2k-1, 2k) with xi_{2k} = -xi_{2k-1}: the zeroth- and second-order
 // terms are even in xi, the first- and third-order terms odd, so each pair
-// costs one even and one odd sum.  `base` is added to m0 (rho0 when the
-// stored value is f itself, 0 when it is the deviation from rest).
+// costs one even and one odd sum.  Every coefficient is multiplied by the
+// smallest weight first, which leaves the populations of that weight without
+// a multiplication and the others with an exact one (the weights of a
+// lattice differ by powers of two).  The odd part is a sum over the axes,
+// 3 xi_a T_a(xi_b^2, xi_c^2), with
+//   T_a = m1_a + (xi_b^2 - cs^2) A_abb / 3 + (xi_c^2 - cs^2) A_acc / 3
+// shared by all directions with the same squares, plus the xyz term where
+// the lattice carries it: D3Q19 needs 30 operations for the three T_a and one
+// per edge pair, against five per edge pair with every basis element added
+// to every direction.  The factors the terms enter with (1.5, 4.5, 9, 3, and
+// 2/9 against 1/9) are exact or exact multiples of each other, so that mass
+// and momentum are conserved to the rounding of the sums: scaled each by the
+// weight instead (1.5 w, 4.5 w, 3 w rounded apart) they drift.  `base` is
+// added to m0 (rho0 when the stored value is f itself, 0 when it is the
+// deviation from rest).
 template <class L, class R>
-__device__ __forceinline__ void rebuild_all(const Coeffs<L, R>& c, const R bk[L::K], R base,
-                                            R out[L::Q]) {
-  const R tr = c.m2[0] + c.m2[1] + (L::D == 3 ? c.m2[2] : (R)0);
+__device__ __forceinline__ void rebuild_all(const Coeffs<L, R>& c, R base, R out[L::Q]) {
+  constexpr double we = L::w(L::Q - 1);
+  R m2[6], t1[3];
+#pragma unroll
+  for (int a = 0; a < 6; ++a) m2[a] = (R)we * c.m2[a];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) t1[a] = (R)we * c.m1[a];
+  const R tr = m2[0] + m2[1] + (L::D == 3 ? m2[2] : (R)0);
   // even part at xi = 0: m0 - cs^2 tr / (2 cs^4) = m0 - 1.5 tr
-  const R e0 = base + c.m0 - (R)1.5 * tr;
-  const R m1s[3] = {(R)3 * c.m1[0], (R)3 * c.m1[1], (R)3 * c.m1[2]};
-  const R d2[3] = {(R)4.5 * c.m2[0], (R)4.5 * c.m2[1], (R)4.5 * c.m2[2]};
-  const R o2[3] = {(R)9 * c.m2[3], (R)9 * c.m2[4], (R)9 * c.m2[5]};
-  if constexpr (L::KH > 0) {
+  const R e0 = (R)we * (base + c.m0) - (R)1.5 * tr;
+  // third-order coefficients A_abb, A_acc over their norms: (xyy, xzz),
+  // (xxy, yzz), (xxz, yyz); D3Q19 resolves their sum and difference only
+  constexpr int kA[3][2] = {{kXYY, kXZZ}, {kXXY, kYZZ}, {kXXZ, kYYZ}};
+  // T[a][p + 2 q]: p, q the squares of xi along the other two axes in order
+  R T[3][4];
+  static_for<0, L::D>([&](auto AX) {
+    constexpr int a = decltype(AX)::value;
+    constexpr int k0 = kA[a][0], k1 = kA[a][1];
+    constexpr R lo = (R)(1.0 / 9.0), hi = (R)(2.0 / 9.0);
+    if constexpr (L::D == 2) {
+      constexpr int j0 = a == 0 ? 1 : 0;
+      const R A0 = (R)(we / basis_norm<L>(j0)) * c.m3[k0];
+      T[a][0] = t1[a] - lo * A0;
+      T[a][1] = t1[a] + hi * A0;
+    } else {
+      R A0, A1;
+      if constexpr (L::Q == 19) {
+        constexpr int kb = a == 0 ? 2 : (a == 1 ? 0 : 4);
+        constexpr double ns = we / basis_norm<L>(kb), nd = we / basis_norm<L>(kb + 1);
+        A0 = (R)(ns + nd) * c.m3[k0] + (R)(ns - nd) * c.m3[k1];
+        A1 = (R)(ns - nd) * c.m3[k0] + (R)(ns + nd) * c.m3[k1];
+      } else {
+        A0 = (R)(we / basis_norm<L>(k0)) * c.m3[k0];
+        A1 = (R)(we / basis_norm<L>(k1)) * c.m3[k1];
+      }
+      const R tl = t1[a] - lo * A1, th = t1[a] + hi * A1;
+      T[a][0] = tl - lo * A0;
+      T[a][1] = tl + hi * A0;
+      T[a][2] = th - lo * A0;
+      if constexpr (L::Q == 27) T[a][3] = th + hi * A0;
+    }
+  });
+  R X = (R)0;
+  if constexpr (L::Q == 27) X = (R)(we / (3.0 * basis_norm<L>(kXYZ))) * c.m3[kXYZ];
+  // orders 4 to 6, scaled (odd orders by a third, with the rest of the odd
+  // part)
+  R mh[L::KH > 0 ? L::KH : 1];
+  static_for<0, L::KH>([&](auto KK) {
+    constexpr int k = decltype(KK)::value;
+    mh[k] = (R)(high_order(L::high(k)) % 2 == 0 ? we : we / 3.0) * c.mh[k];
+  });
+  {
     R h0 = e0;
     static_for<0, L::KH>([&](auto KK) {
       constexpr double hk = high_h<L>(0, decltype(KK)::value);
-      if constexpr (hk != 0.0) h0 += (R)hk * c.mh[decltype(KK)::value];
+      if constexpr (hk != 0.0) h0 += (R)hk * mh[decltype(KK)::value];
     });
-    out[0] = (R)L::w(0) * h0;
-  } else {
-    out[0] = (R)L::w(0) * e0;
+    out[0] = (R)(L::w(0) / we) * h0;
   }
   static_for<0, (L::Q - 1) / 2>([&](auto K) {
     constexpr int i = 1 + 2 * decltype(K)::value;
     constexpr Dir v = L::dir(i);
     R even = e0;
-    if constexpr (v.x != 0) even += d2[0];
-    if constexpr (v.y != 0) even += d2[1];
-    if constexpr (v.z != 0) even += d2[2];
-    if constexpr (v.x * v.y > 0) even += o2[0];
-    if constexpr (v.x * v.y < 0) even -= o2[0];
-    if constexpr (v.x * v.z > 0) even += o2[1];
-    if constexpr (v.x * v.z < 0) even -= o2[1];
-    if constexpr (v.y * v.z > 0) even += o2[2];
-    if constexpr (v.y * v.z < 0) even -= o2[2];
-    R odd = (R)0;
-    if constexpr (v.x > 0) odd += m1s[0];
-    if constexpr (v.x < 0) odd -= m1s[0];
-    if constexpr (v.y > 0) odd += m1s[1];
-    if constexpr (v.y < 0) odd -= m1s[1];
-    if constexpr (v.z > 0) odd += m1s[2];
-    if constexpr (v.z < 0) odd -= m1s[2];
-    static_for<0, L::K>([&](auto KK) {
-      constexpr double hk = basis_h<L>(i, decltype(KK)::value);
-      if constexpr (hk != 0.0) odd += (R)hk * bk[decltype(KK)::value];
-    });
+    if constexpr (v.x != 0) even += (R)4.5 * m2[0];
+    if constexpr (v.y != 0) even += (R)4.5 * m2[1];
+    if constexpr (v.z != 0) even += (R)4.5 * m2[2];
+    if constexpr (v.x * v.y > 0) even += (R)9 * m2[3];
+    if constexpr (v.x * v.y < 0) even -= (R)9 * m2[3];
+    if constexpr (v.x * v.z > 0) even += (R)9 * m2[4];
+    if constexpr (v.x * v.z < 0) even -= (R)9 * m2[4];
+    if constexpr (v.y * v.z > 0) even += (R)9 * m2[5];
+    if constexpr (v.y * v.z < 0) even -= (R)9 * m2[5];
+    constexpr int tx = v.y * v.y + 2 * v.z * v.z, ty = v.x * v.x + 2 * v.z * v.z,
+                  tz = v.x * v.x + 2 * v.y * v.y;
+    // one axis at least is nonzero: the first starts the sum
+    R odd;
+    if constexpr (v.x > 0) odd = T[0][tx];
+    if constexpr (v.x < 0) odd = -T[0][tx];
+    if constexpr (v.x == 0 && v.y > 0) odd = T[1][ty];
+    if constexpr (v.x != 0 && v.y > 0) odd += T[1][ty];
+    if constexpr (v.x != 0 && v.y < 0) odd -= T[1][ty];
+    if constexpr (v.x == 0 && v.y == 0) odd = T[2][tz];
+    if constexpr ((v.x != 0 || v.y != 0) && v.z > 0) odd += T[2][tz];
+    if constexpr ((v.x != 0 || v.y != 0) && v.z < 0) odd -= T[2][tz];
+    if constexpr (v.x * v.y * v.z > 0) odd += X;
+    if constexpr (v.x * v.y * v.z < 0) odd -= X;
     // orders 4 to 6: even orders join the even part, odd orders the odd
     static_for<0, L::KH>([&](auto KK) {
       constexpr int k = decltype(KK)::value;
       constexpr double hk = high_h<L>(i, k);
       if constexpr (hk != 0.0) {
         if constexpr (high_order(L::high(k)) % 2 == 0)
-          even += (R)hk * c.mh[k];
+          even += (R)hk * mh[k];
         else
-          odd += (R)hk * c.mh[k];
+          odd += (R)hk * mh[k];
       }
     });
-    constexpr R w = (R)L::w(i);
-    out[i] = w * (even + odd);
-    out[i + 1] = w * (even - odd);
+    constexpr R w = (R)(L::w(i) / we);
+    out[i] = w * (even + (R)3 * odd);
+    out[i + 1] = w * (even - (R)3 * odd);
   });
-}
-
-// third-order set -> basis coefficients c_k / N_k
-template <class L, class R>
-__device__ __forceinline__ void basis_coeffs(const R m3[7], R bk[L::K]) {
-#pragma unroll
-  for (int k = 0; k < L::K; ++k) {
-    const Basis3 b = L::basis(k);
-    R v = (R)b.sgn[0] * m3[b.idx[0]];
-    if (b.n == 2) v += (R)b.sgn[1] * m3[b.idx[1]];
-    bk[k] = v * (R)(1.0 / basis_norm<L>(k));
-  }
 }
 
 // Third-order non-equilibrium coefficients from the recursion eq.
@@ -477,35 +533,56 @@ __device__ __forceinline__ void cube3(R rho, const R u[3], R t[7]) {
 // differences d = h_i - h_{i+1} of its deviations h = f - w rho0:
 // drho = sum h, j = sum h xi = sum d xi_i, P = sum h xi xi = sum s xi_i xi_i
 // (P = Pi - rho0 cs^2 I).
+// The sums over the two edge pairs of a plane and over the corner pairs are
+// formed once and shared (D3Q19 36 additions instead of 45, D3Q27 54
+// instead of 76).
 template <class L, class R>
 __device__ __forceinline__ void pair_moments(R h0, const R s[(L::Q - 1) / 2],
                                              const R d[(L::Q - 1) / 2], R& drho, R j[3],
                                              R P[6]) {
-  drho = h0;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) j[a] = (R)0;
-#pragma unroll
-  for (int a = 0; a < 6; ++a) P[a] = (R)0;
-  static_for<0, (L::Q - 1) / 2>([&](auto K) {
-    constexpr int k = decltype(K)::value;
-    constexpr Dir v = L::dir(1 + 2 * k);
-    drho += s[k];
-    if constexpr (v.x > 0) j[0] += d[k];
-    if constexpr (v.x < 0) j[0] -= d[k];
-    if constexpr (v.y > 0) j[1] += d[k];
-    if constexpr (v.y < 0) j[1] -= d[k];
-    if constexpr (v.z > 0) j[2] += d[k];
-    if constexpr (v.z < 0) j[2] -= d[k];
-    if constexpr (v.x != 0) P[0] += s[k];
-    if constexpr (v.y != 0) P[1] += s[k];
-    if constexpr (v.z != 0) P[2] += s[k];
-    if constexpr (v.x * v.y > 0) P[3] += s[k];
-    if constexpr (v.x * v.y < 0) P[3] -= s[k];
-    if constexpr (v.x * v.z > 0) P[4] += s[k];
-    if constexpr (v.x * v.z < 0) P[4] -= s[k];
-    if constexpr (v.y * v.z > 0) P[5] += s[k];
-    if constexpr (v.y * v.z < 0) P[5] -= s[k];
-  });
+  constexpr int A = L::D;  // pairs 0 ... D - 1 are the axes, then the edges
+  static_assert(L::dir(2 * A + 1).x == 1 && L::dir(2 * A + 1).y == 1 &&
+                    L::dir(2 * A + 3).x == 1 && L::dir(2 * A + 3).y == -1,
+                "edge pairs in the order (+,+), (+,-)");
+  const R sxy = s[A] + s[A + 1];
+  P[3] = s[A] - s[A + 1];
+  j[0] = d[0] + (d[A] + d[A + 1]);
+  j[1] = d[1] + (d[A] - d[A + 1]);
+  if constexpr (L::D == 2) {
+    P[0] = s[0] + sxy;
+    P[1] = s[1] + sxy;
+    drho = h0 + s[0] + P[1];
+    j[2] = P[2] = P[4] = P[5] = (R)0;
+  } else {
+    const R sxz = s[5] + s[6], syz = s[7] + s[8];
+    P[4] = s[5] - s[6];
+    P[5] = s[7] - s[8];
+    j[0] += d[5] + d[6];
+    j[1] += d[7] + d[8];
+    j[2] = d[2] + (d[5] - d[6]);
+    j[2] += d[7] - d[8];
+    P[0] = s[0] + sxy + sxz;
+    P[1] = s[1] + sxy + syz;
+    P[2] = s[2] + sxz + syz;
+    drho = h0 + s[0] + s[1] + s[2] + sxy + sxz + syz;
+    if constexpr (L::Q == 27) {
+      // corner pairs (+,+,+), (+,+,-), (+,-,+), (-,+,+)
+      const R s01 = s[9] + s[10], s23 = s[11] + s[12];
+      const R t01 = s[9] - s[10], t23 = s[11] - s[12];
+      const R sc = s01 + s23;
+      drho += sc;
+      P[0] += sc;
+      P[1] += sc;
+      P[2] += sc;
+      P[3] += s01 - s23;
+      P[4] += t01 + t23;
+      P[5] += t01 - t23;
+      const R d01 = d[9] + d[10], d23 = d[11] - d[12];
+      j[0] += d01 + d23;
+      j[1] += d01 - d23;
+      j[2] += (d[9] - d[10]) + (d[11] + d[12]);
+    }
+  }
 }
 
 // Moments from the deviations h_i.
@@ -645,9 +722,7 @@ __device__ __forceinline__ R collide_coeffs(R drho, R j[3], const R P[6], R omeg
 // the stored value is f itself, 0 when it is the deviation from rest).
 template <class L, class R>
 __device__ __forceinline__ void rebuild_from(const Coeffs<L, R>& c, R base, R out[L::Q]) {
-  R bk[L::K];
-  basis_coeffs<L, R>(c.m3, bk);
-  rebuild_all<L, R>(c, bk, base, out);
+  rebuild_all<L, R>(c, base, out);
 }
 
 // Collision of one cell: coefficients and rebuild.

@@ -239,6 +239,13 @@ struct BatchHeader {
 
 hipError_t launch_sweep(int lattice, int storage, const SweepHost& h, int block,
                         hipStream_t st);
+// two steps of a fully periodic 3D grid in one pass: h.src at t -> h.dst at
+// t + 2, workgroups marching zc planes each (pair3d.hip)
+hipError_t launch_pair3d(int lattice, int storage, const SweepHost& h, uint32_t zc,
+                         hipStream_t st);
+// planes per workgroup for a grid of q velocities on a device with `cus`
+// compute units, 0 where two one-step sweeps are faster
+uint32_t pair3d_planes(int q, int storage, uint32_t nx, uint32_t ny, uint32_t nz, uint32_t cus);
 // persistent batched sweep: grid of `grid` workgroups of `block` threads
 // variant = lattice code * 16 + storage * 2 + (general path ? 1 : 0)
 // s_off: offset added to the device-side step index for this launch

@@ -294,6 +294,9 @@ int lbm_create(const lbm_config* cfg, lbm_ctx** out) {
   ctx->cfg = *cfg;
   ctx->stream = (hipStream_t)cfg->stream;
   ctx->device = cfg->device;
+  if (hipDeviceGetAttribute(&ctx->cus, hipDeviceAttributeMultiprocessorCount, cfg->device) !=
+      hipSuccess)
+    ctx->cus = 0;
   inlet_velocity(ctx->cfg, ctx->uin);
   rc = make_levels(ctx);
   if (rc != LBM_OK) {
@@ -445,8 +448,35 @@ int sweep_level(lbm_ctx* ctx, int l, hipStream_t st) {
   return LBM_OK;
 }
 
+// Planes per workgroup of the two-step sweep of level 0, 0 where steps are
+// taken one at a time.
+static uint32_t pair_planes(const lbm_ctx* ctx) {
+  const lbm_config& c = ctx->cfg;
+  if (ctx->nlevels > 1 || has_halo(c) || moment_storage(c.storage) ||
+      c.lattice == LBM_D2Q9 || (c.flags & (LBM_BGK | LBM_MRT)))
+    return 0;
+  if (sweep_args(ctx, 0, 0, 0).general) return 0;
+  return pair3d_planes(c.lattice, c.storage, (uint32_t)c.nx, (uint32_t)c.ny, (uint32_t)c.nz,
+                       (uint32_t)ctx->cus);
+}
+
+// Two steps of level 0 in one launch.
+static hipError_t launch_pair(const lbm_ctx* ctx, int src_buf, uint32_t zc, hipStream_t st) {
+  return launch_pair3d(sweep_lattice(ctx->cfg), ctx->cfg.storage, sweep_args(ctx, 0, src_buf, 0),
+                       zc, st);
+}
+
 // Enqueue n single-grid steps eagerly.
 static int step_eager(lbm_ctx* ctx, int64_t n, hipStream_t st) {
+  const uint32_t zc = n > 1 ? pair_planes(ctx) : 0;
+  for (; zc && n >= 2; n -= 2) {
+    Level& L = ctx->lv[0];
+    hipError_t e = launch_pair(ctx, L.cur, zc, st);
+    if (e != hipSuccess) return hip_error(e, "two-step sweep launch");
+    L.cur ^= 1;
+    L.t += 2;
+    ctx->t += 2;
+  }
   for (int64_t s = 0; s < n; ++s) {
     int rc = ctx->nlevels > 1 ? refined_coarse_step(ctx, st) : sweep_level(ctx, 0, st);
     if (rc != LBM_OK) return rc;
@@ -550,7 +580,12 @@ static int step_graph(lbm_ctx* ctx, int64_t chunks, hipStream_t st) {
     hipError_t e = hipStreamBeginCapture(ctx->capture_stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_error(e, "hipStreamBeginCapture");
     int buf = L.cur;
-    for (int64_t s = 0; s < kGraphSteps; ++s) {
+    const uint32_t zc = pair_planes(ctx);
+    for (int64_t s = 0; zc && s < kGraphSteps && e == hipSuccess; s += 2) {
+      e = launch_pair(ctx, buf, zc, ctx->capture_stream);
+      buf ^= 1;
+    }
+    for (int64_t s = 0; !zc && s < kGraphSteps; ++s) {
       SweepHost h = sweep_args(ctx, 0, buf, (uint64_t)(L.t + 1 + s));
       e = launch_step_kernel(ctx, h, ctx->block, ctx->capture_stream);
       if (e != hipSuccess) break;

@@ -57,6 +57,7 @@ constexpr int kMaxLevels = LBM_MAX_LEVELS;
 struct lbm_ctx {
   lbm_config cfg{};
   int device = 0;
+  int cus = 0;  // compute units of the device
   hipStream_t stream = nullptr;
   hipStream_t capture_stream = nullptr;
   int nlevels = 1;
