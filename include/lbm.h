@@ -226,8 +226,8 @@ int lbm_init(lbm_ctx* ctx, int level, const double* rho, const double* u,
 
 /* Enqueue n coarse steps (level l + 1 takes two steps per step of level l
  * on a refined context; n <= 1 with LBM_HALO faces, else LBM_EINVAL).  Where
- * it is faster, two steps are taken in one pass over the grid; results do not
- * depend on it (bitwise) nor on how n is split over calls.
+ * it is faster, two or four steps are taken in one pass over the grid; results
+ * do not depend on it (bitwise) nor on how n is split over calls.
  * Returns after enqueueing.  Kernel-side instability is recorded in a sticky
  * flag reported by lbm_sync / lbm_moments. */
 int lbm_step(lbm_ctx* ctx, int64_t n);
@@ -344,7 +344,8 @@ int lbm_set_interface(lbm_ctx* ctx, int level, const void* in);
 /* Serving: advance ctxs[k] by steps[k] coarse steps, k < n, sharing
  * launches between contexts: the contexts are grouped by lattice, storage,
  * sweep path (fully periodic or not) and workgroup size, and each group
- * advances through one persistent launch per step.  The first group runs
+ * advances through persistent launches, each of one step (D2Q9: of two or
+ * four, then single ones).  The first group runs
  * on the contexts' stream, the others concurrently on streams the library
  * owns, ordered after and joined back into the contexts' stream with
  * events, so work queued on that stream before the call precedes every

@@ -7,304 +7,9 @@
 #include "kernels.hpp"
 #include "launch.hpp"
 #include "reduce.hpp"
+#include "sweep.hpp"
 
 namespace hrlbm {
-
-// sweep arguments of one storage format from the format-neutral host block
-template <class S>
-__host__ __device__ inline SweepArgs<S> to_args_dev(const SweepHost& h);
-
-// direction index for a velocity given at run time (only used after a
-// free-slip reflection)
-template <class L>
-struct DirTable {
-  int v[27];
-  constexpr DirTable() : v() {
-    for (int z = -1; z <= 1; ++z)
-      for (int y = -1; y <= 1; ++y)
-        for (int x = -1; x <= 1; ++x)
-          v[(x + 1) + 3 * (y + 1) + 9 * (z + 1)] = find_dir<L>(x, y, z);
-  }
-};
-template <class L>
-__device__ __forceinline__ int dir_rt(int x, int y, int z) {
-  constexpr DirTable<L> t{};
-  return t.v[(x + 1) + 3 * (y + 1) + 9 * (z + 1)];
-}
-
-// ------------------------------------------------------------------------
-// Pull under the face rules and the mask (left side of eq. optimizedLB read
-// backwards): the source of population i is x - xi_i, mapped axis by axis
-// (periodic wrap, free-slip reflection with the population mirrored,
-// zero-gradient clamp, or the neighbour subdomain's values through a halo
-// face); a link whose source is SOLID is bounced back halfway from this
-// cell.  Applied as corrections to the periodic pull already in raw[]: only
-// the directions whose source crosses a non-periodic face, or (for cells
-// flagged kNearSolid) is SOLID, are loaded again.
-// ------------------------------------------------------------------------
-template <class L, class S>
-__device__ __forceinline__ void pull_fixup(const SweepArgs<S>& a, uint32_t x, uint32_t y,
-                                           uint32_t z, uint32_t c, bool near_solid,
-                                           typename S::T raw[L::Q]) {
-  const uint64_t P = a.pstride;
-  const uint32_t dims[3] = {a.nx, a.ny, a.nz};
-  static_for<1, L::Q>([&](auto I) {
-    constexpr int i = decltype(I)::value;
-    constexpr Dir v = L::dir(i);
-    constexpr int vv[3] = {v.x, v.y, v.z};
-    int32_t s[3] = {(int32_t)x - v.x, (int32_t)y - v.y, (int32_t)z - v.z};
-    bool flip[3] = {false, false, false};
-    bool cross = false;
-    int hs = -1;  // halo side crossed (only the last axis has halo faces)
-#pragma unroll
-    for (int ax = 0; ax < L::D; ++ax) {
-      if (vv[ax] == 0) continue;
-      const int32_t n = (int32_t)dims[ax];
-      const bool lo = s[ax] < 0, hi = s[ax] >= n;
-      if (lo || hi) {
-        const int32_t bc = a.face[2 * ax + (hi ? 1 : 0)];
-        if (bc == kPeriodic) {
-          s[ax] = lo ? s[ax] + n : s[ax] - n;
-        } else {
-          s[ax] = lo ? 0 : n - 1;
-          flip[ax] = (bc == kFreeSlip);
-          if (bc == kHalo) hs = hi ? 1 : 0;
-          cross = true;
-        }
-      }
-    }
-    const uint32_t src = ((uint32_t)s[2] * a.ny + (uint32_t)s[1]) * a.nx + (uint32_t)s[0];
-    if (near_solid && hs < 0 && (a.mask[src] & kKindBits) == kSolid) {
-      // halfway bounce-back: the population that left this cell towards
-      // the wall comes back reversed (same weight, so the same shift)
-      constexpr int o = opposite<L>(i);
-      raw[i] = load_pop(a.src + (uint64_t)o * P, c);
-    } else if (cross) {
-      int pop = i;
-      if (flip[0] || flip[1] || flip[2])
-        pop = dir_rt<L>(flip[0] ? -v.x : v.x, flip[1] ? -v.y : v.y,
-                        flip[2] ? -v.z : v.z);
-      if (hs >= 0) {
-        // the source lies in the neighbour's face plane (mapped on the
-        // other axes as above); a free-slip flip acts on the other axes
-        // only, so the row is one of four known at compile time
-        constexpr int r00 = halo_rank<L>(i);
-        constexpr int r10 = halo_rank<L>(find_dir<L>(-v.x, v.y, v.z));
-        constexpr int r01 = halo_rank<L>(find_dir<L>(v.x, -v.y, v.z));
-        constexpr int r11 = halo_rank<L>(find_dir<L>(-v.x, -v.y, v.z));
-        const int r = flip[0] ? (flip[1] ? r11 : r10) : (flip[1] ? r01 : r00);
-        const uint32_t pc = L::D == 3 ? (uint32_t)s[1] * a.nx + (uint32_t)s[0] : (uint32_t)s[0];
-        const typename S::T* rb = hs ? a.hrecv[1] : a.hrecv[0];
-        raw[i] = load_pop(rb + (uint64_t)r * a.hplane, pc);
-      } else {
-        raw[i] = load_pop(a.src + (uint64_t)pop * P, src);
-      }
-    }
-  });
-}
-
-// Halo faces on the periodic path (every other face periodic, no mask): a
-// face-plane cell replaces the populations the periodic pull wrapped across
-// a halo face by the neighbour's values, from the receive buffer at the
-// source wrapped on the other axes.
-template <class L, class S>
-__device__ __forceinline__ void halo_pull_periodic(const SweepArgs<S>& a, uint32_t x,
-                                                   uint32_t y, uint32_t z,
-                                                   typename S::T raw[L::Q]) {
-  const uint32_t zl = L::D == 3 ? z : y, nl = L::D == 3 ? a.nz : a.ny;
-  const bool lo = zl == 0 && a.hrecv[0], hi = zl + 1 == nl && a.hrecv[1];
-  if (!lo && !hi) return;
-  static_for<1, L::Q>([&](auto I) {
-    constexpr int i = decltype(I)::value;
-    constexpr Dir v = L::dir(i);
-    constexpr int vl = last_component<L>(v);
-    if constexpr (vl != 0) {
-      if ((vl > 0 && lo) || (vl < 0 && hi)) {
-        int32_t sx = (int32_t)x - v.x;
-        if (sx < 0) sx += (int32_t)a.nx;
-        if (sx >= (int32_t)a.nx) sx -= (int32_t)a.nx;
-        uint32_t pc = (uint32_t)sx;
-        if constexpr (L::D == 3) {
-          int32_t sy = (int32_t)y - v.y;
-          if (sy < 0) sy += (int32_t)a.ny;
-          if (sy >= (int32_t)a.ny) sy -= (int32_t)a.ny;
-          pc += (uint32_t)sy * a.nx;
-        }
-        const typename S::T* rb = vl > 0 ? a.hrecv[0] : a.hrecv[1];
-        raw[i] = load_pop(rb + (uint64_t)halo_rank<L>(i) * a.hplane, pc);
-      }
-    }
-  });
-}
-
-// Pack of a face-plane cell's post-collision populations that leave
-// through a halo face into that face's send buffer.
-template <class L, class S>
-__device__ __forceinline__ void halo_pack(const SweepArgs<S>& a, uint32_t c, uint32_t zl,
-                                          uint32_t nl, const typename S::R post[L::Q]) {
-  using T = typename S::T;
-  const uint32_t pc = c - zl * a.hplane;
-  const bool lo = zl == 0 && a.hsend[0], hi = zl + 1 == nl && a.hsend[1];
-  static_for<1, L::Q>([&](auto I) {
-    constexpr int i = decltype(I)::value;
-    constexpr int vl = last_component<L>(L::dir(i));
-    constexpr int r = halo_rank<L>(i);
-    if constexpr (vl < 0) {
-      if (lo) a.hsend[0][(uint64_t)r * a.hplane + pc] = narrow<T>(post[i]);
-    } else if constexpr (vl > 0) {
-      if (hi) a.hsend[1][(uint64_t)r * a.hplane + pc] = narrow<T>(post[i]);
-    }
-  });
-}
-
-// Pull of all populations of a cell whose neighbours need no face rule or
-// bounce-back: offsets to the x-1 / x+1 (etc.) neighbours, with wrap-around
-// on periodic axes.  kNt: rows are whole 64-cell tiles (nx a multiple of
-// 64), so each wavefront's cells are one aligned row segment, and the
-// populations with no x velocity are loaded with the non-temporal hint.
-template <class L, class S, bool kNt>
-__device__ __forceinline__ void pull_periodic(const SweepArgs<S>& a, uint32_t c, uint32_t x,
-                                              uint32_t y, uint32_t z,
-                                              typename S::T raw[L::Q]) {
-  const uint64_t P = a.pstride;
-  const int32_t nx = (int32_t)a.nx, nxy = (int32_t)(a.nx * a.ny);
-  const int32_t ox_m = x == 0 ? nx - 1 : -1;
-  const int32_t ox_p = x == a.nx - 1 ? -(nx - 1) : 1;
-  const int32_t oy_m = y == 0 ? (int32_t)(a.ny - 1) * nx : -nx;
-  const int32_t oy_p = y == a.ny - 1 ? -(int32_t)(a.ny - 1) * nx : nx;
-  int32_t oz_m = 0, oz_p = 0;
-  if constexpr (L::D == 3) {
-    oz_m = z == 0 ? (int32_t)(a.nz - 1) * nxy : -nxy;
-    oz_p = z == a.nz - 1 ? -(int32_t)(a.nz - 1) * nxy : nxy;
-  }
-  static_for<0, L::Q>([&](auto I) {
-    constexpr int i = decltype(I)::value;
-    constexpr Dir v = L::dir(i);
-    int32_t off = 0;
-    if constexpr (v.x > 0) off += ox_m;
-    if constexpr (v.x < 0) off += ox_p;
-    if constexpr (v.y > 0) off += oy_m;
-    if constexpr (v.y < 0) off += oy_p;
-    if constexpr (v.z > 0) off += oz_m;
-    if constexpr (v.z < 0) off += oz_p;
-    // With aligned rows, a population with no x velocity comes from a row
-    // segment aligned with this wavefront's cells, whose lines no other
-    // wavefront reads; the non-temporal hint keeps those lines from
-    // displacing the ones at the segment ends of the other populations,
-    // which the neighbouring wavefront reads too (1 % faster on D3Q19 FP32
-    // 256^3, 6 % on D2Q9 2048 x 1024; with the hint on every population,
-    // no faster; on unaligned rows, where wavefronts share those lines
-    // too, 3 % slower).  A template choice, not a branch: the compiler
-    // merges identical loads on the two sides of a branch and drops the
-    // hint.
-    if constexpr (kNt && v.x == 0)
-      raw[i] = load_pop_nt(a.src + (uint64_t)i * P, (uint32_t)((int32_t)c + off));
-    else
-      raw[i] = load_pop(a.src + (uint64_t)i * P, (uint32_t)((int32_t)c + off));
-  });
-}
-
-// Refinement records of one cell's pre-collision moments: on the parent
-// side the nodes on the child box's boundary planes, on the child side the
-// band its parent's IMPORT nodes filter.
-template <class L, class S>
-__device__ __forceinline__ void record_moments(const SweepArgs<S>& a,
-                                               const CellMoments<typename S::R>& mo,
-                                               uint32_t x, uint32_t y, uint32_t z, uint32_t c) {
-  const int64_t r =
-      a.rec ? record_index<L::D>(a.rec_off, a.rec_dim, a.box_lo, a.box_hi, x, y, z) : -1;
-  if (r >= 0) {
-    // ten contiguous values per node (read together by the RING fill)
-    typename S::R* rr = a.rec + (uint64_t)r * 10;
-    rr[0] = mo.drho;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) rr[1 + k] = mo.u[k];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) rr[4 + k] = mo.a2[k];
-  }
-  if (a.recf && in_import_band<L::D>(x, y, z, a.nx, a.ny, a.nz)) {
-    // ten contiguous values per node: the IMPORT filter reads a node's
-    // stress components together
-    typename S::R* rc = a.recf + (uint64_t)c * 10;
-    rc[0] = mo.drho;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) rc[1 + k] = mo.u[k];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) rc[4 + k] = mo.a2[k];
-  }
-}
-
-// Interpolation points and weights of a child node coordinate k along one
-// axis (the child box starts at parent coordinate lo): a coincident node
-// copies its parent node; a midpoint takes the local cubic (-1, 9, 9, -1)/16.
-__device__ __forceinline__ int axis_points(int32_t lo, uint32_t k, int32_t pts[4],
-                                           float wts[4]) {
-  if ((k & 1u) == 0) {
-    pts[0] = lo + (int32_t)(k >> 1);
-    wts[0] = 1.0f;
-    return 1;
-  }
-  const int32_t j = lo + (int32_t)(k >> 1);
-  pts[0] = j - 1;
-  pts[1] = j;
-  pts[2] = j + 1;
-  pts[3] = j + 2;
-  wts[0] = -1.0f / 16.0f;
-  wts[1] = 9.0f / 16.0f;
-  wts[2] = 9.0f / 16.0f;
-  wts[3] = -1.0f / 16.0f;
-  return 4;
-}
-
-// RING node state (eq. couplingFC): interpolated rho~, u~, Pi~_neq (cubic
-// in space, linear in time: wa Ma + wb Mb of the parent's two recorded
-// time levels), Pi_neq rescaled by alpha_cf = tau_f / (2 tau_c), then
-// f = f^{eqH}(rho~, u~) + (1 - 1/tau_f) f^{neqH}(alpha_cf Pi~_neq, u~),
-// encoded for storage.  k: the node's coordinates on the child level.
-template <class L, class S>
-__device__ __forceinline__ void ring_node(const typename S::R* Ma, const typename S::R* Mb,
-                                          typename S::R wa, typename S::R wb,
-                                          typename S::R alpha, typename S::R omega1,
-                                          typename S::R rho0, const int32_t lo[3],
-                                          const int32_t rec_off[3], const uint32_t rec_dim[3],
-                                          const uint32_t k[3], typename S::T vals[L::Q]) {
-  using R = typename S::R;
-  int32_t pts[3][4];
-  float wts[3][4];
-  int np[3];
-  for (int ax = 0; ax < 3; ++ax) {
-    if (ax < L::D) {
-      np[ax] = axis_points(lo[ax], k[ax], pts[ax], wts[ax]);
-    } else {
-      np[ax] = 1;
-      pts[ax][0] = rec_off[ax];
-      wts[ax][0] = 1.0f;
-    }
-  }
-  R m[10];
-  for (int q = 0; q < 10; ++q) m[q] = (R)0;
-  for (int i2 = 0; i2 < np[2]; ++i2)
-    for (int i1 = 0; i1 < np[1]; ++i1)
-      for (int i0 = 0; i0 < np[0]; ++i0) {
-        const uint64_t r =
-            ((uint64_t)(pts[2][i2] - rec_off[2]) * rec_dim[1] +
-             (uint64_t)(pts[1][i1] - rec_off[1])) * rec_dim[0] +
-            (uint64_t)(pts[0][i0] - rec_off[0]);
-        const R w = (R)wts[0][i0] * (R)wts[1][i1] * (R)wts[2][i2];
-        for (int q = 0; q < 10; ++q) {
-          const uint64_t o = r * 10 + (uint64_t)q;
-          m[q] += w * (wa * Ma[o] + wb * Mb[o]);
-        }
-      }
-  R u[3] = {m[1], m[2], L::D == 3 ? m[3] : (R)0};
-  R a2[6];
-  for (int q = 0; q < 6; ++q) a2[q] = alpha * m[4 + q];
-  if (L::D == 2) a2[2] = a2[4] = a2[5] = (R)0;
-  R out[L::Q];
-  rebuild_state<L, R>(m[0], rho0, u, a2, omega1, out);
-#pragma unroll
-  for (int i = 0; i < L::Q; ++i) vals[i] = encode<S>(out[i], (R)L::w(i) * rho0);
-}
 
 // ------------------------------------------------------------------------
 // The sweep: pull-stream + (sponge) + regularized collision + store.
@@ -323,23 +28,13 @@ __device__ __forceinline__ void sweep_cell(const SweepArgs<S>& a, uint32_t c) {
   const uint32_t z = fast_div(row, a.div_ny);
   const uint32_t y = row - z * a.ny;
   const uint64_t P = a.pstride;
-  // the rebuilt values are produced directly in the storage domain
-  const R base = S::kShifted ? (R)0 : a.rho0;
-
   T raw[Q];
   R post[Q];
-  R rho, drho, j[3], Pm[6];
+  R rho;
+  uint8_t m = kFluid;
   if constexpr (!kGeneral) {
     pull_periodic<L, S, kNt>(a, c, x, y, z, raw);
     if (a.hrecv[0] || a.hrecv[1]) halo_pull_periodic<L, S>(a, x, y, z, raw);
-    stored_moments<L, S>(raw, a.rho0, drho, j, Pm);
-    if constexpr (L::kColl == kCollBGK)
-      rho = collide_bgk<L, S>(raw, drho, j, a.omega1, a.rho0, (R)0, a.rho_ref, a.uref, post);
-    else if constexpr (L::kColl == kCollMRT)
-      rho = collide_mrt<L, S>(raw, drho, j, a.omega1, a.rho0, post);
-    else
-      rho = collide_moments<L, R, false>(drho, j, Pm, a.omega1, a.rho0, (R)0, a.rho_ref,
-                                         a.uref, base, post);
   } else {
     // a plain tile (wave-uniform, read through the scalar cache) needs no
     // mask; otherwise the interior pull is issued before the mask decides:
@@ -347,8 +42,7 @@ __device__ __forceinline__ void sweep_cell(const SweepArgs<S>& a, uint32_t c) {
     // mask's latency
     const uint32_t tile = (uint32_t)__builtin_amdgcn_readfirstlane(c) >> 6;
     const bool plain = a.tiles && a.tiles[tile];
-    uint8_t m = kFluid;  // (every level on this path carries a mask)
-    if (!plain) m = a.mask ? a.mask[c] : kFluid;
+    if (!plain) m = a.mask ? a.mask[c] : kFluid;  // (every level on this path carries a mask)
     pull_periodic<L, S, kNt>(a, c, x, y, z, raw);
     const uint8_t kind = m & kKindBits;
     if (kind == kRing && a.ring_Ma) {
@@ -365,55 +59,12 @@ __device__ __forceinline__ void sweep_cell(const SweepArgs<S>& a, uint32_t c) {
       });
       return;
     }
-    if (kind == kSolid || kind >= kCovered) return;
-    // one rebuild for every kind of cell keeps the kernel's code compact
-    // (the comparators collide without it)
-    Coeffs<L, R> cf;
-    bool rebuild = true;
-    if (kind == kInlet) {
-      // f^{eqH}(rho0, U u_dir (1 + noise r)), r from SplitMix64
-      R u[3];
-      const uint64_t bidx =
-          ((a.t_new * (uint64_t)a.lstride + (uint64_t)a.level) * (uint64_t)a.ncell + c) * 3ull;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const R r = (R)splitmix_pm1(a.seed, bidx + (uint64_t)k);
-        u[k] = a.uin[k] * ((R)1 + a.noise * r);
-      }
-      if (L::D == 2) u[2] = (R)0;
-      const R zero6[6] = {(R)0, (R)0, (R)0, (R)0, (R)0, (R)0};
-      state_coeffs<L, R>((R)0, a.rho0, u, zero6, (R)0, cf);
-      rho = a.rho0;
-    } else {
-      if (m & (kNearFace | kNearSolid))
-        pull_fixup<L, S>(a, x, y, z, c, (m & kNearSolid) != 0, raw);
-      stored_moments<L, S>(raw, a.rho0, drho, j, Pm);
-      R chi = (R)0, rref = a.rho_ref, uref[3] = {a.uref[0], a.uref[1], a.uref[2]};
-      if (m & kFieldSponge) {
-        chi = a.sp[c];
-        rref = a.sp[a.ncell + c];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) uref[k] = a.sp[(uint64_t)(2 + k) * a.ncell + c];
-      } else if (a.chi_max != (R)0) {
-        chi = sponge_chi<R>(a.sponge, a.chi_max, x, y, z, a.nx, a.ny, a.nz);
-      }
-      if constexpr (L::kColl == kCollBGK) {
-        rho = collide_bgk<L, S>(raw, drho, j, a.omega1, a.rho0, chi, rref, uref, post);
-        rebuild = false;
-      } else if constexpr (L::kColl == kCollMRT) {
-        rho = collide_mrt<L, S>(raw, drho, j, a.omega1, a.rho0, post);
-        rebuild = false;
-      } else {
-        // (the moments are always returned in registers; a conditional
-        // pointer here would push them to scratch memory)
-        CellMoments<R> mo;
-        rho = collide_coeffs<L, R, true>(drho, j, Pm, a.omega1, a.rho0, chi, rref, uref, cf,
-                                         &mo);
-        if (a.rec || a.recf) record_moments<L, S>(a, mo, x, y, z, c);
-      }
-    }
-    if (rebuild) rebuild_from<L, R>(cf, base, post);
   }
+  auto fixup = [&](T* r) {
+    if (m & (kNearFace | kNearSolid))
+      pull_fixup<L, S>(a, x, y, z, c, (m & kNearSolid) != 0, r);
+  };
+  if (!collide_cell<L, S, kGeneral>(a, c, x, y, z, m, a.t_new, raw, post, rho, fixup)) return;
   // stability watchdog: a rare, benign racy store of 1
   if (!(rho > (R)0) || !(rho < (R)1e30)) a.status[0] = 1;
   {
@@ -700,10 +351,10 @@ __global__ void k_set_pop(PopArgs a) {
 template <class L, class S, bool kGeneral>
 __device__ __forceinline__ void batch_cell(const BatchJob& J, int32_t s, uint32_t c) {
   SweepArgs<S> a = to_args_dev<S>(J.h);
-  const int p = (J.cur0 + s) & 1;
+  const int p = (int)(J.cur0 + J.flips0 + s) & 1;
   a.src = (const typename S::T*)J.buf[p];
   a.dst = (typename S::T*)J.buf[p ^ 1];
-  a.t_new = J.t0 + (uint64_t)s + 1ull;
+  a.t_new = J.t0 + (uint64_t)(J.done0 + s) + 1ull;
   a.ncell = J.h.nx * J.h.ny * J.h.nz;
   a.div_nx = FastDiv{J.div_nx[0], J.div_nx[1], J.div_nx[2]};
   a.div_ny = FastDiv{J.div_ny[0], J.div_ny[1], J.div_ny[2]};
@@ -742,7 +393,7 @@ __global__ void __launch_bounds__(1024)
       }
     }
     const BatchJob& J = jobs[lo];
-    if ((int64_t)s >= J.steps) continue;
+    if ((int64_t)s >= J.steps - J.done0) continue;
     const uint32_t c = (tile - J.tile_begin) * blockDim.x + threadIdx.x;
     if (c >= J.h.nx * J.h.ny * J.h.nz) continue;
     batch_cell<L, S, kGeneral>(J, s, c);
@@ -999,80 +650,9 @@ __global__ void k_import(ImportArgs ia) {
 // ------------------------------------------------------------------------
 // Host launchers
 // ------------------------------------------------------------------------
-template <class S>
-static SweepArgs<S> to_args(const SweepHost& h) {
-  return to_args_dev<S>(h);
-}
-
-template <class S>
-__host__ __device__ inline SweepArgs<S> to_args_dev(const SweepHost& h) {
-  using T = typename S::T;
-  using R = typename S::R;
-  SweepArgs<S> a;
-  a.src = (const T*)h.src;
-  a.dst = (T*)h.dst;
-  a.mask = h.mask;
-  a.tiles = h.tiles;
-  a.status = h.status;
-  a.nx = h.nx;
-  a.ny = h.ny;
-  a.nz = h.nz;
-  a.ncell = h.nx * h.ny * h.nz;
-  a.pstride = h.pstride;
-#if !defined(__HIP_DEVICE_COMPILE__)
-  a.div_nx = make_fastdiv(h.nx);
-  a.div_ny = make_fastdiv(h.ny);
-#endif
-  a.omega1 = (R)(1.0 - 1.0 / h.tau);
-  a.rho0 = (R)h.rho0;
-  a.chi_max = (R)h.chi_max;
-  a.rho_ref = (R)h.rho_ref;
-  for (int k = 0; k < 3; ++k) {
-    a.uref[k] = (R)h.uref[k];
-    a.uin[k] = (R)h.uin[k];
-  }
-  a.noise = (R)h.noise;
-  for (int f = 0; f < 6; ++f) {
-    a.face[f] = h.face[f];
-    a.sponge[f] = h.sponge[f];
-  }
-  a.seed = h.seed;
-  a.t_new = h.t_new;
-  a.level = h.level;
-  a.lstride = h.lstride;
-  a.ntiles = 0;
-  a.xcd_group = 1;
-  a.rec = (R*)h.rec;
-  a.recf = (R*)h.recf;
-  a.sp = (const R*)h.sp;
-  for (int k = 0; k < 3; ++k) {
-    a.rec_off[k] = h.rec_off[k];
-    a.rec_dim[k] = h.rec_dim[k];
-    a.box_lo[k] = h.box_lo[k];
-    a.box_hi[k] = h.box_hi[k];
-  }
-  a.rec_n = h.rec_n;
-  a.ring_Ma = (const R*)h.ring_Ma;
-  a.ring_Mb = (const R*)h.ring_Mb;
-  a.ring_wa = (R)h.ring_wa;
-  a.ring_wb = (R)h.ring_wb;
-  a.ring_alpha = (R)h.ring_alpha;
-  for (int k = 0; k < 3; ++k) {
-    a.ring_lo[k] = h.ring_lo[k];
-    a.ring_off[k] = h.ring_off[k];
-    a.ring_dim[k] = h.ring_dim[k];
-  }
-  for (int k = 0; k < 2; ++k) {
-    a.hrecv[k] = (const T*)h.hrecv[k];
-    a.hsend[k] = (T*)h.hsend[k];
-  }
-  a.hplane = h.hplane;
-  return a;
-}
-
 template <class L, class S>
 static hipError_t launch_sweep_t(const SweepHost& h, int block, hipStream_t st) {
-  SweepArgs<S> a = to_args<S>(h);
+  SweepArgs<S> a = to_args_dev<S>(h);
   const uint32_t blocks = (a.ncell + block - 1) / block;
   a.ntiles = blocks;
   a.xcd_group = block < 256 ? 256u / (uint32_t)block : 1u;
@@ -1223,8 +803,27 @@ static hipError_t batch_dispatch(int variant, bool query, const BatchJob* jobs,
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_batch(int variant, const BatchJob* jobs, BatchHeader* hdr, int32_t s_off,
-                        int block, int grid, hipStream_t st) {
+// the fused kernel of a batch variant
+static Multi2d fused_batch(int variant, int fused) {
+  Multi2d m{};
+  m.lattice = variant / 16;
+  m.storage = (variant / 2) % 8;
+  m.general = variant & 1;
+  m.steps = fused;
+  return m;
+}
+
+hipError_t launch_batch(int variant, int fused, const BatchJob* jobs, BatchHeader* hdr,
+                        int32_t s_off, int block, int grid, hipStream_t st) {
+  if (fused > 1) {
+    Multi2d m = fused_batch(variant, fused);
+    m.jobs = jobs;
+    m.hdr = hdr;
+    m.s_off = s_off;
+    m.grid = grid;
+    m.st = st;
+    return launch_multi2d(m);
+  }
   return batch_dispatch(variant, false, jobs, hdr, s_off, block, grid, st, nullptr);
 }
 
@@ -1233,14 +832,20 @@ hipError_t launch_batch_bump(BatchHeader* hdr, int32_t by, hipStream_t st) {
   return hipGetLastError();
 }
 
-int batch_grid(int variant, int block) {
+int batch_grid(int variant, int fused, int block) {
   int dev = 0, cus = 0, per = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return 0;
-  if (batch_dispatch(variant, true, nullptr, nullptr, 0, block, 0, nullptr, &per) != hipSuccess ||
-      per < 1)
-    per = 1;
+  hipError_t e;
+  if (fused > 1) {
+    Multi2d m = fused_batch(variant, fused);
+    m.query = &per;
+    e = launch_multi2d(m);
+  } else {
+    e = batch_dispatch(variant, true, nullptr, nullptr, 0, block, 0, nullptr, &per);
+  }
+  if (e != hipSuccess || per < 1) per = 1;
   return cus * per;
 }
 

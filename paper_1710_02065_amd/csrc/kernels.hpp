@@ -311,6 +311,10 @@ struct Coeffs {
   R mh[L::KH > 0 ? L::KH : 1];  // order >= 4 (full order only), divided by N_k
 };
 
+// Whether p holds on any active lane (uniform, so that a branch on it is a
+// scalar one).
+__device__ __forceinline__ bool any_lane(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0; }
+
 // Compile-time loop (the index is a constant in the body).
 template <int B, int E, class F>
 __device__ __forceinline__ void static_for(F&& f) {
@@ -922,8 +926,7 @@ __device__ __forceinline__ R sponge_chi(const int32_t* width, R chi_max,
     const R s = (f & 1) ? (R)pos[a] : (R)(n[a] - 1u - pos[a]);
     const R s0 = (R)(int64_t)(n[a] - (uint32_t)W);
     if (s < s0) continue;
-    const R Lw = (R)W;
-    const R d = (s - s0) / Lw;
+    const R d = (s - s0) * ((R)1 / (R)W);
     const R sig = (R)(3125.0 / 256.0) * ((R)1 - d) * (d * d) * (d * d);
     best = sig > best ? sig : best;
   }

@@ -225,6 +225,10 @@ struct BatchJob {
   int32_t cur0;         // buffer holding the state at batch start
   uint64_t t0;          // time index at batch start
   int64_t steps;        // steps this job takes in the batch
+  // the first done0 of them are taken several at a time in flips0 fused
+  // launches (0: none), the others one at a time
+  int64_t done0, flips0;
+  uint32_t ftile_begin;  // first fused tile of this job
   uint32_t tile_begin;  // first tile of this job in the work list
   uint32_t ntiles;
   uint32_t div_nx[3], div_ny[3];  // fast-division constants (d, m, s)
@@ -234,7 +238,7 @@ struct BatchHeader {
   uint32_t njobs;
   uint32_t total_tiles;
   int32_t step;  // base of the step index s within the batch (plus the launch's offset)
-  int32_t pad;
+  uint32_t total_ftiles;  // fused tiles of all jobs
 };
 
 hipError_t launch_sweep(int lattice, int storage, const SweepHost& h, int block,
@@ -246,14 +250,33 @@ hipError_t launch_pair3d(int lattice, int storage, const SweepHost& h, uint32_t 
 // planes per workgroup for a grid of q velocities on a device with `cus`
 // compute units, 0 where two one-step sweeps are faster
 uint32_t pair3d_planes(int q, int storage, uint32_t nx, uint32_t ny, uint32_t nz, uint32_t cus);
+// Several steps of D2Q9 grids in one pass (multi2d.hip): a single grid h
+// (h->src at t -> h->dst at t + steps, the first step producing h->t_new), or
+// with jobs the fused tiles of a batch; with query the workgroups per CU.
+struct Multi2d {
+  int lattice, storage, steps;
+  bool general;
+  const SweepHost* h;
+  const BatchJob* jobs;
+  const BatchHeader* hdr;
+  int32_t s_off;
+  int grid;
+  int* query;
+  hipStream_t st;
+};
+hipError_t launch_multi2d(const Multi2d& m);
+// steps per pass (1: one-step sweeps) and tiles of a grid
+int multi2d_steps(int storage, bool general, uint32_t nx, uint32_t ny, bool batch);
+uint32_t multi2d_tiles(uint32_t nx, uint32_t ny);
 // persistent batched sweep: grid of `grid` workgroups of `block` threads
 // variant = lattice code * 16 + storage * 2 + (general path ? 1 : 0)
 // s_off: offset added to the device-side step index for this launch
-hipError_t launch_batch(int variant, const BatchJob* jobs, BatchHeader* hdr, int32_t s_off,
-                        int block, int grid, hipStream_t st);
+// with fused > 1 a launch takes that many steps of every job (done0, flips0)
+hipError_t launch_batch(int variant, int fused, const BatchJob* jobs, BatchHeader* hdr,
+                        int32_t s_off, int block, int grid, hipStream_t st);
 // advance the device-side step index by `by`
 hipError_t launch_batch_bump(BatchHeader* hdr, int32_t by, hipStream_t st);
-int batch_grid(int variant, int block);  // resident workgroups on the device
+int batch_grid(int variant, int fused, int block);  // resident workgroups on the device
 void fill_fastdiv(uint32_t d, uint32_t out[3]);
 hipError_t launch_init(int lattice, int storage, const InitArgs& a, uint32_t n,
                        hipStream_t st);

@@ -1,0 +1,319 @@
+// Several steps of a D2Q9 grid in one pass over memory.
+//
+// A workgroup takes a tile of OX x OY cells: it pulls and collides the tile
+// and a halo of T - 1 cells from the state at t, keeps the result in LDS, and
+// repeats from there on a region one cell smaller on every side until the
+// tile itself holds the state at t + T, which it stores.  Every cell's step
+// is the one-step sweep's own (walls, open faces, layers, inlet cells), so
+// the values are bitwise those of T single steps.
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "kernels.hpp"
+#include "launch.hpp"
+#include "sweep.hpp"
+
+namespace hrlbm {
+
+template <class S, int T_, int OY_>
+struct Tile2 {
+  using V = typename S::T;
+  static constexpr int T = T_, OX = 64, OY = OY_, H = T - 1;
+  static constexpr int RX = OX + 2 * H, RY = OY + 2 * H, SLOTS = RX * RY;
+  // with more than two steps, two LDS states alternate
+  static constexpr int NB = T > 2 ? 2 : 1;
+};
+
+// Face rules and bounce-back of a cell whose neighbours are in LDS: `cell` is
+// its slot of population 0, `mask` its slot of the mask, rows RX apart and
+// populations SLOTS apart (see pull_fixup).
+template <class L, class S, int RX, int SLOTS>
+__device__ __forceinline__ void lds_fixup(const SweepArgs<S>& a, uint32_t x, uint32_t y,
+                                          const typename S::T* cell, const uint8_t* mask,
+                                          bool near_solid, typename S::T raw[L::Q]) {
+  const bool on[2][2] = {{a.face[0] != kPeriodic && any_lane(x == 0),
+                          a.face[1] != kPeriodic && any_lane(x + 1 == a.nx)},
+                         {a.face[2] != kPeriodic && any_lane(y == 0),
+                          a.face[3] != kPeriodic && any_lane(y + 1 == a.ny)}};
+  const bool any_solid = any_lane(near_solid);
+  static_for<1, L::Q>([&](auto I) {
+    constexpr int i = decltype(I)::value;
+    constexpr Dir v = L::dir(i);
+    bool reach = any_solid;
+    if constexpr (v.x != 0) reach = reach || on[0][v.x < 0];
+    if constexpr (v.y != 0) reach = reach || on[1][v.y < 0];
+    if (!reach) return;
+    int dx = -v.x, dy = -v.y;
+    bool fx = false, fy = false, cross = false;
+    if constexpr (v.x != 0) {
+      const int f = v.x > 0 ? 0 : 1;
+      if ((v.x > 0 ? x == 0 : x + 1 == a.nx) && a.face[f] != kPeriodic) {
+        dx = 0;
+        fx = a.face[f] == kFreeSlip;
+        cross = true;
+      }
+    }
+    if constexpr (v.y != 0) {
+      const int f = v.y > 0 ? 2 : 3;
+      if ((v.y > 0 ? y == 0 : y + 1 == a.ny) && a.face[f] != kPeriodic) {
+        dy = 0;
+        fy = a.face[f] == kFreeSlip;
+        cross = true;
+      }
+    }
+    const int off = dx + dy * RX;
+    if (near_solid && (mask[off] & kKindBits) == kSolid) {
+      raw[i] = cell[opposite<L>(i) * SLOTS];
+    } else if (cross) {
+      raw[i] = cell[flipped<L, i>(fx, fy, false) * SLOTS + off];
+    }
+  });
+}
+
+template <class L, class S, bool kGeneral, class G>
+__device__ __forceinline__ void multi2d_tile(const SweepArgs<S>& a, uint32_t bx, uint32_t by,
+                                             typename S::T* lds, uint8_t* lmask, uint32_t tid,
+                                             uint32_t nthreads) {
+  using T = typename S::T;
+  using R = typename S::R;
+  constexpr int Q = L::Q;
+  const int32_t nx = (int32_t)a.nx, ny = (int32_t)a.ny;
+  const int32_t x0 = (int32_t)bx * G::OX, y0 = (int32_t)by * G::OY;
+  const int32_t wx = min(G::OX, nx - x0), wy = min(G::OY, ny - y0);
+  const bool px = !kGeneral || a.face[0] == kPeriodic, py = !kGeneral || a.face[2] == kPeriodic;
+  static_for<1, G::T + 1>([&](auto K) {
+    constexpr int k = decltype(K)::value;
+    constexpr int h = G::T - k;  // halo of this step's region
+    constexpr int W = G::OX + 2 * h, N = W * (G::OY + 2 * h);
+    T* const out = lds + (G::NB == 2 && k % 2 == 0 ? Q * G::SLOTS : 0);
+    const T* const in = lds + (G::NB == 2 && k % 2 == 1 ? Q * G::SLOTS : 0);
+    for (int32_t n = (int32_t)tid; n < N; n += (int32_t)nthreads) {
+      const int32_t ly = n / W, lx = n - ly * W;
+      if (lx >= wx + 2 * h || ly >= wy + 2 * h) continue;
+      int32_t gx = x0 - h + lx, gy = y0 - h + ly;
+      // periodic axes wrap (a grid is at least T cells wide); beyond the other
+      // faces there are no cells
+      if (px) {
+        gx += gx < 0 ? nx : (gx >= nx ? -nx : 0);
+      } else if (gx < 0 || gx >= nx) {
+        continue;
+      }
+      if (py) {
+        gy += gy < 0 ? ny : (gy >= ny ? -ny : 0);
+      } else if (gy < 0 || gy >= ny) {
+        continue;
+      }
+      const uint32_t x = (uint32_t)gx, y = (uint32_t)gy, c = y * a.nx + x;
+      const int32_t slot = (ly + (G::H - h)) * G::RX + lx + (G::H - h);
+      T raw[Q];
+      R post[Q], rho;
+      uint8_t m = kFluid;
+      if constexpr (k == 1) {
+        if constexpr (kGeneral) m = a.mask ? a.mask[c] : kFluid;
+        pull_periodic<L, S, false>(a, c, x, y, 0u, raw);
+        if constexpr (kGeneral && G::T > 1) lmask[slot] = m;
+      } else {
+        if constexpr (kGeneral) m = lmask[slot];
+        static_for<0, Q>([&](auto I) {
+          constexpr int i = decltype(I)::value;
+          raw[i] = in[i * G::SLOTS + slot - L::dir(i).x - L::dir(i).y * G::RX];
+        });
+      }
+      auto fixup = [&](T* r) {
+        if (m & (kNearFace | kNearSolid)) {
+          if constexpr (k == 1)
+            pull_fixup<L, S>(a, x, y, 0u, c, (m & kNearSolid) != 0, r);
+          else
+            lds_fixup<L, S, G::RX, G::SLOTS>(a, x, y, in + slot, lmask + slot,
+                                             (m & kNearSolid) != 0, r);
+        }
+      };
+      if (!collide_cell<L, S, kGeneral>(a, c, x, y, 0u, m, a.t_new + (uint64_t)(k - 1), raw, post,
+                                        rho, fixup))
+        continue;
+      // stability watchdog: a rare, benign racy store of 1
+      if (!(rho > (R)0) || !(rho < (R)1e30)) a.status[0] = 1;
+      static_for<0, Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        if constexpr (k == G::T)
+          store_at<false>(a.dst + (uint64_t)i * a.pstride, (uint32_t)(a.pstride * sizeof(T)),
+                      c * (uint32_t)sizeof(T), 0u, narrow<T>(post[i]));
+        else
+          out[i * G::SLOTS + slot] = narrow<T>(post[i]);
+      });
+    }
+    if constexpr (k < G::T) __syncthreads();
+  });
+}
+
+// Whether every cell of a tile's first region is plain fluid outside the
+// layers (wave-uniform): its steps are then the periodic path's.  Reads the
+// 64-cell summaries the region's rows touch, one per lane.
+template <class L, class S, class G>
+__device__ __forceinline__ bool plain_region(const SweepArgs<S>& a, uint32_t bx, uint32_t by) {
+  const int32_t nx = (int32_t)a.nx, ny = (int32_t)a.ny;
+  const int32_t x0 = (int32_t)bx * G::OX, y0 = (int32_t)by * G::OY;
+  const int32_t xl = x0 - G::H, yl = y0 - G::H, xh = min(x0 + G::OX, nx) - 1 + G::H,
+                yh = min(y0 + G::OY, ny) - 1 + G::H;
+  if (xl < 0 || yl < 0 || xh >= nx || yh >= ny || !a.tiles) return false;
+  if (a.chi_max != (typename S::R)0) {
+    if (a.sponge[4] > 0 || a.sponge[5] > 0) return false;
+    if (xl < a.sponge[0] || xh >= nx - a.sponge[1] || yl < a.sponge[2] || yh >= ny - a.sponge[3])
+      return false;
+  }
+  constexpr uint32_t kPer = (G::RX + 63) / 64 + 1;  // summaries a row segment touches
+  bool plain = true;
+  for (uint32_t n = threadIdx.x % 64u; n < kPer * G::RY; n += 64u) {
+    const int32_t y = yl + (int32_t)(n / kPer);
+    if (y > yh) continue;
+    const uint32_t first = (uint32_t)(y * nx + xl) >> 6, last = (uint32_t)(y * nx + xh) >> 6;
+    const uint32_t t = first + n % kPer;
+    if (t <= last) plain = plain && a.tiles[t];
+  }
+  return __all(plain);
+}
+
+// Rows of a tile and threads of a workgroup for T steps: the LDS of the
+// intermediate states limits the rows.
+template <int T>
+struct Shape2 {
+  static constexpr int OY = 8, NT = T == 4 ? 512 : 256;
+};
+// Wavefronts per SIMD: what the LDS of a CU admits.
+template <class S, int T>
+struct Waves2 {
+  static constexpr int value =
+      sizeof(typename S::T) == 8 ? 2 : sizeof(typename S::T) == 4 ? (T == 4 ? 4 : 5) : 6;
+};
+
+template <class L, class S, bool kGeneral, class G>
+__device__ __forceinline__ void multi2d_any(const SweepArgs<S>& a, uint32_t bx, uint32_t by,
+                                            typename S::T* lds, uint8_t* lmask,
+                                            uint32_t nthreads) {
+  if constexpr (kGeneral) {
+    if (plain_region<L, S, G>(a, bx, by)) {
+      multi2d_tile<L, S, false, G>(a, bx, by, lds, lmask, threadIdx.x, nthreads);
+      return;
+    }
+  }
+  multi2d_tile<L, S, kGeneral, G>(a, bx, by, lds, lmask, threadIdx.x, nthreads);
+}
+
+template <class L, class S, bool kGeneral, int T>
+__global__ void __launch_bounds__(Shape2<T>::NT)
+    __attribute__((amdgpu_waves_per_eu(Waves2<S, T>::value)))
+    k_multi2d(const SweepArgs<S> a, uint32_t tiles_x, uint32_t ntile) {
+  using G = Tile2<S, T, Shape2<T>::OY>;
+  __shared__ typename S::T lds[G::NB * L::Q * G::SLOTS];
+  __shared__ uint8_t lmask[kGeneral ? G::SLOTS : 1];
+  // each XCD takes a contiguous range of tiles
+  const uint32_t k = blockIdx.x % 8u, per = ntile / 8u, rem = ntile % 8u;
+  const uint32_t b = k * per + min(k, rem) + blockIdx.x / 8u;
+  multi2d_any<L, S, kGeneral, G>(a, b % tiles_x, b / tiles_x, lds, lmask, Shape2<T>::NT);
+}
+
+// ------------------------------------------------------------------------
+// The same tiles over the (job, tile) list of a batch (serving): a fixed grid
+// of workgroups walks the list; launch s advances every job that has at least
+// (s + 1) T steps by T.  Tiles go to the XCDs in runs of kRun consecutive
+// ones, so that neighbours meet in one L2 and every XCD gets a share of every
+// job.
+// ------------------------------------------------------------------------
+template <class L, class S, bool kGeneral, int T>
+__global__ void __launch_bounds__(Shape2<T>::NT)
+    __attribute__((amdgpu_waves_per_eu(Waves2<S, T>::value)))
+    k_batch2d(const BatchJob* __restrict__ jobs, const BatchHeader* __restrict__ hdr,
+              int32_t s_off) {
+  using G = Tile2<S, T, Shape2<T>::OY>;
+  constexpr uint32_t kRun = 32;
+  __shared__ typename S::T lds[G::NB * L::Q * G::SLOTS];
+  __shared__ uint8_t lmask[kGeneral ? G::SLOTS : 1];
+  const int32_t s = hdr->step + s_off;
+  const uint32_t njobs = hdr->njobs, total = hdr->total_ftiles;
+  const uint32_t xcd = blockIdx.x % 8u, per = (gridDim.x + 7u - xcd) / 8u;
+  uint32_t lo = 0;  // job of the previous tile: this workgroup's tiles increase
+  for (uint32_t j = blockIdx.x / 8u;; j += per) {
+    const uint32_t first = (j / kRun * 8u + xcd) * kRun, tile = first + j % kRun;
+    if (first >= total) break;
+    if (tile >= total) continue;
+    if (lo + 1 < njobs && jobs[lo + 1].ftile_begin <= tile) {
+      uint32_t hi = njobs;
+      ++lo;
+      while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (jobs[mid].ftile_begin <= tile) lo = mid; else hi = mid;
+      }
+    }
+    const BatchJob& J = jobs[lo];
+    if ((int64_t)s >= J.flips0) continue;
+    SweepArgs<S> a = to_args_dev<S>(J.h);
+    const int p = (J.cur0 + s) & 1;
+    a.src = (const typename S::T*)J.buf[p];
+    a.dst = (typename S::T*)J.buf[p ^ 1];
+    a.t_new = J.t0 + (uint64_t)s * T + 1ull;
+    const uint32_t n = tile - J.ftile_begin, tx = (J.h.nx + G::OX - 1) / G::OX;
+    multi2d_any<L, S, kGeneral, G>(a, n % tx, n / tx, lds, lmask, Shape2<T>::NT);
+    __syncthreads();  // LDS is rewritten by the next tile
+  }
+}
+
+// Steps per pass.  A batch takes four at a time, but two on the general path
+// of the 4- and 8-byte storages, whose larger halo costs more there than the
+// second pass it saves; a single grid takes four on that path too while its
+// tiles do not fill the device.  us per step, one at a time / two / four:
+// periodic 4000 x 3001 FP32 147 / 90 / 75, FP16S 79 / 58 / 51, 128 x 128
+// FP64 3.2 / 2.8 / 2.0; cylinder channel 2048 x 1024 FP32 32 / 18 / 21,
+// FP16S 26 / 20 / 19, FP64 60 / 38 / 44; 1000 x 700 FP32 14.4 / 13.9 / 11.9.
+int multi2d_steps(int storage, bool general, uint32_t nx, uint32_t ny, bool batch) {
+  if (nx < 4 || ny < 4) return 1;  // the halo wraps once
+  if (!general || storage == 3) return 4;
+  return !batch && (uint64_t)nx * ny < (1u << 20) ? 4 : 2;
+}
+uint32_t multi2d_tiles(uint32_t nx, uint32_t ny) { return (nx + 63) / 64 * ((ny + 7) / 8); }
+
+template <class L, class S, bool kGeneral, int T>
+static hipError_t multi2d_g(const Multi2d& m) {
+  const dim3 block(Shape2<T>::NT);
+  if (m.query)
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(m.query, k_batch2d<L, S, kGeneral, T>,
+                                                        Shape2<T>::NT, 0);
+  if (m.jobs) {
+    hipLaunchKernelGGL((k_batch2d<L, S, kGeneral, T>), dim3(m.grid), block, 0, m.st, m.jobs,
+                       m.hdr, m.s_off);
+  } else {
+    const uint32_t tx = (m.h->nx + 63) / 64, n = multi2d_tiles(m.h->nx, m.h->ny);
+    hipLaunchKernelGGL((k_multi2d<L, S, kGeneral, T>), dim3(n), block, 0, m.st,
+                       to_args_dev<S>(*m.h), tx, n);
+  }
+  return hipGetLastError();
+}
+
+template <class L, class S>
+static hipError_t multi2d_t(const Multi2d& m) {
+  if (m.general)
+    return m.steps == 4 ? multi2d_g<L, S, true, 4>(m) : multi2d_g<L, S, true, 2>(m);
+  return m.steps == 4 ? multi2d_g<L, S, false, 4>(m) : multi2d_g<L, S, false, 2>(m);
+}
+
+template <class L>
+static hipError_t multi2d_l(const Multi2d& m) {
+  switch (m.storage) {
+    case 0: return multi2d_t<L, StoreF64>(m);
+    case 1: return multi2d_t<L, StoreF32>(m);
+    case 2: return multi2d_t<L, StoreF32S>(m);
+    case 3: return multi2d_t<L, StoreF16S>(m);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_multi2d(const Multi2d& m) {
+  if (m.steps != 2 && m.steps != 4) return hipErrorInvalidValue;
+  switch (m.lattice) {
+    case 9: return multi2d_l<Lattice<9>>(m);
+    case kFullOrderCode + 9: return multi2d_l<Lattice<9, true>>(m);
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace hrlbm

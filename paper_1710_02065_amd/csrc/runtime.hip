@@ -448,34 +448,60 @@ int sweep_level(lbm_ctx* ctx, int l, hipStream_t st) {
   return LBM_OK;
 }
 
-// Planes per workgroup of the two-step sweep of level 0, 0 where steps are
-// taken one at a time.
-static uint32_t pair_planes(const lbm_ctx* ctx) {
+// Steps of level 0 taken in one pass (1: one-step sweeps), and the planes per
+// workgroup of the 3D pass.
+struct Fused {
+  int steps = 1;
+  uint32_t zc = 0;
+};
+
+static Fused fused_steps(const lbm_ctx* ctx) {
   const lbm_config& c = ctx->cfg;
+  Fused f;
   if (ctx->nlevels > 1 || has_halo(c) || moment_storage(c.storage) ||
-      c.lattice == LBM_D2Q9 || (c.flags & (LBM_BGK | LBM_MRT)))
-    return 0;
-  if (sweep_args(ctx, 0, 0, 0).general) return 0;
-  return pair3d_planes(c.lattice, c.storage, (uint32_t)c.nx, (uint32_t)c.ny, (uint32_t)c.nz,
-                       (uint32_t)ctx->cus);
+      (c.flags & (LBM_BGK | LBM_MRT)))
+    return f;
+  const bool general = sweep_args(ctx, 0, 0, 0).general;
+  if (c.lattice == LBM_D2Q9) {
+    f.steps = multi2d_steps(c.storage, general, (uint32_t)c.nx, (uint32_t)c.ny, false);
+  } else if (!general) {
+    f.zc = pair3d_planes(c.lattice, c.storage, (uint32_t)c.nx, (uint32_t)c.ny, (uint32_t)c.nz,
+                         (uint32_t)ctx->cus);
+    f.steps = f.zc ? 2 : 1;
+  }
+  return f;
 }
 
-// Two steps of level 0 in one launch.
-static hipError_t launch_pair(const lbm_ctx* ctx, int src_buf, uint32_t zc, hipStream_t st) {
-  return launch_pair3d(sweep_lattice(ctx->cfg), ctx->cfg.storage, sweep_args(ctx, 0, src_buf, 0),
-                       zc, st);
+// One pass of level 0 from buffer src_buf, its first step producing t_new.
+static hipError_t launch_fused(const lbm_ctx* ctx, const Fused& f, int src_buf, uint64_t t_new,
+                               hipStream_t st) {
+  const SweepHost h = sweep_args(ctx, 0, src_buf, t_new);
+  if (ctx->cfg.lattice == LBM_D2Q9) {
+    Multi2d m{};
+    m.lattice = sweep_lattice(ctx->cfg);
+    m.storage = ctx->cfg.storage;
+    m.steps = f.steps;
+    m.general = h.general;
+    m.h = &h;
+    m.st = st;
+    return launch_multi2d(m);
+  }
+  return launch_pair3d(sweep_lattice(ctx->cfg), ctx->cfg.storage, h, f.zc, st);
 }
 
 // Enqueue n single-grid steps eagerly.
 static int step_eager(lbm_ctx* ctx, int64_t n, hipStream_t st) {
-  const uint32_t zc = n > 1 ? pair_planes(ctx) : 0;
-  for (; zc && n >= 2; n -= 2) {
+  Fused f = n > 1 ? fused_steps(ctx) : Fused{};
+  while (f.steps > 1 && n > 1) {
+    // (what is left of a pass of four steps: one of two, then a single step)
+    if (n < f.steps) f.steps = 2;
+    n -= f.steps;
     Level& L = ctx->lv[0];
-    hipError_t e = launch_pair(ctx, L.cur, zc, st);
-    if (e != hipSuccess) return hip_error(e, "two-step sweep launch");
+    hipError_t e = launch_fused(ctx, f, L.cur, (uint64_t)(L.t + 1), st);
+    if (e != hipSuccess) return hip_error(e, "fused sweep launch");
     L.cur ^= 1;
-    L.t += 2;
-    ctx->t += 2;
+    L.t += f.steps;
+    ctx->t += f.steps;
   }
   for (int64_t s = 0; s < n; ++s) {
     int rc = ctx->nlevels > 1 ? refined_coarse_step(ctx, st) : sweep_level(ctx, 0, st);
@@ -580,12 +606,12 @@ static int step_graph(lbm_ctx* ctx, int64_t chunks, hipStream_t st) {
     hipError_t e = hipStreamBeginCapture(ctx->capture_stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_error(e, "hipStreamBeginCapture");
     int buf = L.cur;
-    const uint32_t zc = pair_planes(ctx);
-    for (int64_t s = 0; zc && s < kGraphSteps && e == hipSuccess; s += 2) {
-      e = launch_pair(ctx, buf, zc, ctx->capture_stream);
+    const Fused f = fused_steps(ctx);
+    for (int64_t s = 0; f.steps > 1 && s < kGraphSteps && e == hipSuccess; s += f.steps) {
+      e = launch_fused(ctx, f, buf, (uint64_t)(L.t + 1 + s), ctx->capture_stream);
       buf ^= 1;
     }
-    for (int64_t s = 0; !zc && s < kGraphSteps; ++s) {
+    for (int64_t s = 0; f.steps == 1 && s < kGraphSteps; ++s) {
       SweepHost h = sweep_args(ctx, 0, buf, (uint64_t)(L.t + 1 + s));
       e = launch_step_kernel(ctx, h, ctx->block, ctx->capture_stream);
       if (e != hipSuccess) break;

@@ -35,7 +35,8 @@ struct BatchRunner {
   BatchHeader* h_hdr = nullptr;
   hipEvent_t staged = nullptr;  // the last upload finished reading staging
   hipStream_t capture = nullptr;
-  std::map<std::pair<int, int>, GraphEntry> graphs;  // (kernel variant, block)
+  // (kernel variant, block, or -fused steps)
+  std::map<std::pair<int, int>, GraphEntry> graphs;
   std::map<std::pair<int, int>, int> grids;
   // Lanes: the second and later groups of a batch run on runners of their
   // own with their own streams, concurrently with the first group (on the
@@ -126,17 +127,19 @@ static int ensure_capacity(BatchRunner* r, size_t n) {
   return LBM_OK;
 }
 
-static int graph_for(BatchRunner* r, int variant, int block, int grid, GraphEntry** out) {
-  auto key = std::make_pair(variant, block);
+static int graph_for(BatchRunner* r, int variant, int fused, int block, int grid,
+                     GraphEntry** out) {
+  const int launches = kBatchGraphSteps / fused;
+  auto key = std::make_pair(variant, fused > 1 ? -fused : block);
   auto it = r->graphs.find(key);
   if (it == r->graphs.end()) {
     GraphEntry g{};
     hipError_t e = hipStreamBeginCapture(r->capture, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_error(e, "batch capture begin");
-    // steps base + 0 ... base + kBatchGraphSteps - 1, then base += kBatchGraphSteps
-    for (int k = 0; k < kBatchGraphSteps && e == hipSuccess; ++k)
-      e = launch_batch(variant, r->d_jobs, r->d_hdr, (int32_t)k, block, grid, r->capture);
-    if (e == hipSuccess) e = launch_batch_bump(r->d_hdr, (int32_t)kBatchGraphSteps, r->capture);
+    // launches base + 0 ... base + launches - 1, then base += launches
+    for (int k = 0; k < launches && e == hipSuccess; ++k)
+      e = launch_batch(variant, fused, r->d_jobs, r->d_hdr, (int32_t)k, block, grid, r->capture);
+    if (e == hipSuccess) e = launch_batch_bump(r->d_hdr, (int32_t)launches, r->capture);
     hipGraph_t graph = nullptr;
     hipError_t e2 = hipStreamEndCapture(r->capture, &graph);
     if (e != hipSuccess) return hip_error(e, "batch launch during capture");
@@ -159,6 +162,59 @@ static int batch_variant(const lbm_ctx* c) {
   return sweep_lattice(c->cfg) * 16 + c->cfg.storage * 2 + (h.general ? 1 : 0);
 }
 
+// Steps a group's fused launches take at a time (1: none).
+static int group_fused(const lbm_ctx* c) {
+  if (c->cfg.lattice != LBM_D2Q9 || (c->cfg.flags & (LBM_BGK | LBM_MRT))) return 1;
+  return multi2d_steps(c->cfg.storage, sweep_args(c, 0, 0, 0).general, (uint32_t)c->cfg.nx,
+                       (uint32_t)c->cfg.ny, true);
+}
+
+// The batch table entry of a context.
+static void fill_job(BatchJob& J, lbm_ctx* c, int64_t steps, int block, uint32_t tile_begin,
+                     uint32_t ftile_begin) {
+  const Level& L = c->lv[0];
+  std::memset(&J, 0, sizeof J);
+  J.h = sweep_args(c, 0, L.cur, 0);
+  J.buf[0] = L.buf[0];
+  J.buf[1] = L.buf[1];
+  J.storage = c->cfg.storage;
+  J.cur0 = L.cur;
+  J.t0 = (uint64_t)L.t;
+  J.steps = steps;
+  // (a grid too narrow for the fused tiles takes single steps in any group)
+  const int fused = group_fused(c);
+  if (fused > 1) {
+    J.flips0 = steps / fused;
+    J.done0 = J.flips0 * fused;
+  }
+  J.tile_begin = tile_begin;
+  J.ftile_begin = ftile_begin;
+  J.ntiles = (uint32_t)((L.N + block - 1) / block);
+  fill_fastdiv((uint32_t)L.nx, J.div_nx);
+  fill_fastdiv((uint32_t)L.ny, J.div_ny);
+}
+
+// What the launches of a group cover.
+struct GroupPlan {
+  int fused = 1;           // steps per fused launch
+  int64_t fused_launches = 0, single_launches = 0;
+  uint32_t tiles = 0, ftiles = 0;
+  void add(const lbm_ctx* c, const BatchJob& J) {
+    fused = std::max(fused, group_fused(c));
+    fused_launches = std::max(fused_launches, J.flips0);
+    single_launches = std::max(single_launches, J.steps - J.done0);
+    tiles += J.ntiles;
+    ftiles += multi2d_tiles((uint32_t)c->cfg.nx, (uint32_t)c->cfg.ny);
+  }
+};
+
+// A context after its steps of a batch.
+static void advance_job(lbm_ctx* c, const BatchJob& J) {
+  c->lv[0].t += J.steps;
+  c->lv[0].cur ^= (int)((J.flips0 + J.steps - J.done0) & 1);
+  c->t += J.steps;
+}
+
 // One batch of contexts sharing a kernel variant and workgroup size.
 static int run_group(BatchRunner* r, const std::vector<std::pair<lbm_ctx*, int64_t>>& grp) {
   lbm_ctx* c0 = grp[0].first;
@@ -168,30 +224,15 @@ static int run_group(BatchRunner* r, const std::vector<std::pair<lbm_ctx*, int64
   if (rc != LBM_OK) return rc;
   hipError_t e = hipEventSynchronize(r->staged);
   if (e != hipSuccess) return hip_error(e, "batch staging wait");
-  uint32_t tiles = 0;
-  int64_t max_steps = 0;
+  GroupPlan plan;
   for (size_t k = 0; k < grp.size(); ++k) {
-    lbm_ctx* c = grp[k].first;
-    const Level& L = c->lv[0];
-    BatchJob& J = r->h_jobs[k];
-    std::memset(&J, 0, sizeof J);
-    J.h = sweep_args(c, 0, L.cur, 0);
-    J.buf[0] = L.buf[0];
-    J.buf[1] = L.buf[1];
-    J.storage = c->cfg.storage;
-    J.cur0 = L.cur;
-    J.t0 = (uint64_t)L.t;
-    J.steps = grp[k].second;
-    J.tile_begin = tiles;
-    J.ntiles = (uint32_t)((L.N + block - 1) / block);
-    fill_fastdiv((uint32_t)L.nx, J.div_nx);
-    fill_fastdiv((uint32_t)L.ny, J.div_ny);
-    tiles += J.ntiles;
-    max_steps = std::max(max_steps, grp[k].second);
+    fill_job(r->h_jobs[k], grp[k].first, grp[k].second, block, plan.tiles, plan.ftiles);
+    plan.add(grp[k].first, r->h_jobs[k]);
   }
-  if (max_steps == 0) return LBM_OK;
+  if (plan.fused_launches + plan.single_launches == 0) return LBM_OK;
   r->h_hdr->njobs = (uint32_t)grp.size();
-  r->h_hdr->total_tiles = tiles;
+  r->h_hdr->total_tiles = plan.tiles;
+  r->h_hdr->total_ftiles = plan.ftiles;
   r->h_hdr->step = 0;
   e = hipMemcpyAsync(r->d_jobs, r->h_jobs, grp.size() * sizeof(BatchJob),
                      hipMemcpyHostToDevice, r->stream);
@@ -200,35 +241,40 @@ static int run_group(BatchRunner* r, const std::vector<std::pair<lbm_ctx*, int64
                        r->stream);
   if (e == hipSuccess) e = hipEventRecord(r->staged, r->stream);
   if (e != hipSuccess) return hip_error(e, "batch table upload");
-  auto gk = std::make_pair(variant, block);
-  if (!r->grids.count(gk)) r->grids[gk] = batch_grid(variant, block);
-  const int grid = r->grids[gk];
-  if (grid <= 0) return set_error(LBM_EDEVICE, "batch occupancy query failed");
-  int64_t done = 0;
   const bool use_graph = !(c0->cfg.flags & LBM_NO_GRAPH);
-  if (use_graph && max_steps >= kBatchGraphSteps) {
-    GraphEntry* g = nullptr;
-    rc = graph_for(r, variant, block, grid, &g);
-    if (rc != LBM_OK) return rc;
-    for (; done + kBatchGraphSteps <= max_steps; done += kBatchGraphSteps) {
-      e = hipGraphLaunch(g->exec, r->stream);
-      if (e != hipSuccess) return hip_error(e, "batch graph launch");
+  int64_t base = 0;  // the device-side step index, advanced by the graphs
+  // `count` launches, index 0 ... count - 1, of the fused or the one-step
+  // kernel
+  auto launches = [&](int fused, int64_t count) -> int {
+    if (count == 0) return LBM_OK;
+    auto gk = std::make_pair(variant, fused > 1 ? -fused : block);
+    if (!r->grids.count(gk)) r->grids[gk] = batch_grid(variant, fused, block);
+    const int grid = r->grids[gk];
+    if (grid <= 0) return set_error(LBM_EDEVICE, "batch occupancy query failed");
+    int64_t done = 0;
+    const int64_t per = kBatchGraphSteps / fused;
+    // (a graph counts from the index the device holds)
+    if (use_graph && base == 0 && count >= per) {
+      GraphEntry* g = nullptr;
+      const int rc2 = graph_for(r, variant, fused, block, grid, &g);
+      if (rc2 != LBM_OK) return rc2;
+      for (; done + per <= count; done += per) {
+        e = hipGraphLaunch(g->exec, r->stream);
+        if (e != hipSuccess) return hip_error(e, "batch graph launch");
+      }
+      base = done;
     }
-  }
-  // the graphs advanced the device-side base to `done`: the remaining
-  // steps pass their offset from it
-  const int64_t base = done;
-  for (; done < max_steps; ++done) {
-    e = launch_batch(variant, r->d_jobs, r->d_hdr, (int32_t)(done - base), block, grid,
-                     r->stream);
-    if (e != hipSuccess) return hip_error(e, "batch launch");
-  }
-  for (auto& kv : grp) {
-    lbm_ctx* c = kv.first;
-    c->lv[0].t += kv.second;
-    c->lv[0].cur ^= (int)(kv.second & 1);
-    c->t += kv.second;
-  }
+    for (; done < count; ++done) {
+      e = launch_batch(variant, fused, r->d_jobs, r->d_hdr, (int32_t)(done - base), block, grid,
+                       r->stream);
+      if (e != hipSuccess) return hip_error(e, "batch launch");
+    }
+    return LBM_OK;
+  };
+  rc = launches(plan.fused, plan.fused_launches);
+  if (rc == LBM_OK) rc = launches(1, plan.single_launches);
+  if (rc != LBM_OK) return rc;
+  for (size_t k = 0; k < grp.size(); ++k) advance_job(grp[k].first, r->h_jobs[k]);
   return LBM_OK;
 }
 
@@ -286,23 +332,6 @@ __global__ void k_write_table(TableChunk c, BatchHeader* hdr, BatchJob* jobs) {
   if (c.write_hdr) *hdr = c.hdr;
 }
 
-// The batch table entry of a context (as run_group builds it).
-static void fill_job(BatchJob& J, lbm_ctx* c, int64_t steps, uint32_t tile_begin, int block) {
-  const Level& L = c->lv[0];
-  std::memset(&J, 0, sizeof J);
-  J.h = sweep_args(c, 0, L.cur, 0);
-  J.buf[0] = L.buf[0];
-  J.buf[1] = L.buf[1];
-  J.storage = c->cfg.storage;
-  J.cur0 = L.cur;
-  J.t0 = (uint64_t)L.t;
-  J.steps = steps;
-  J.tile_begin = tile_begin;
-  J.ntiles = (uint32_t)((L.N + block - 1) / block);
-  fill_fastdiv((uint32_t)L.nx, J.div_nx);
-  fill_fastdiv((uint32_t)L.ny, J.div_ny);
-}
-
 // One group (contexts order[0..count) sharing kernel variant and workgroup
 // size) through the tables at hdr / jobs: upload by kernel arguments, then
 // one batch launch per step with the step as the launch's offset (the
@@ -313,46 +342,52 @@ static int run_group_noalloc(lbm_ctx* const* ctxs, const int64_t* steps, const i
   const int variant = batch_variant(c0);
   const int block = c0->block;
   hipStream_t st = c0->stream;
-  int64_t max_steps = 0;
-  uint32_t tiles = 0;
+  GroupPlan plan;
   for (int k = 0; k < count; ++k) {
-    const Level& L = ctxs[order[k]]->lv[0];
-    tiles += (uint32_t)((L.N + block - 1) / block);
-    max_steps = std::max(max_steps, steps[order[k]]);
+    BatchJob J;
+    fill_job(J, ctxs[order[k]], steps[order[k]], block, 0, 0);
+    plan.add(ctxs[order[k]], J);
   }
-  if (max_steps == 0) return LBM_OK;
+  if (plan.fused_launches + plan.single_launches == 0) return LBM_OK;
   TableChunk chunk;
-  uint32_t tile_begin = 0;
+  uint32_t tile_begin = 0, ftile_begin = 0;
   for (int k0 = 0; k0 < count; k0 += kTableChunk) {
     std::memset(&chunk, 0, sizeof chunk);
     chunk.count = (uint32_t)std::min(kTableChunk, count - k0);
     for (uint32_t k = 0; k < chunk.count; ++k) {
       const int j = order[k0 + (int)k];
-      fill_job(chunk.jobs[k], ctxs[j], steps[j], tile_begin, block);
+      fill_job(chunk.jobs[k], ctxs[j], steps[j], block, tile_begin, ftile_begin);
       tile_begin += chunk.jobs[k].ntiles;
+      ftile_begin += multi2d_tiles((uint32_t)ctxs[j]->cfg.nx, (uint32_t)ctxs[j]->cfg.ny);
     }
     if (k0 == 0) {
       chunk.write_hdr = 1;
       chunk.hdr.njobs = (uint32_t)count;
-      chunk.hdr.total_tiles = tiles;
+      chunk.hdr.total_tiles = plan.tiles;
+      chunk.hdr.total_ftiles = plan.ftiles;
       chunk.hdr.step = 0;
     }
     hipLaunchKernelGGL(k_write_table, dim3(1), dim3(64), 0, st, chunk, hdr, jobs + k0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_error(e, "allocation-free table upload");
   }
-  const int grid = batch_grid(variant, block);
-  if (grid <= 0) return set_error(LBM_EDEVICE, "batch occupancy query failed");
-  for (int64_t s = 0; s < max_steps; ++s) {
-    hipError_t e = launch_batch(variant, jobs, hdr, (int32_t)s, block, grid, st);
-    if (e != hipSuccess) return hip_error(e, "batch launch");
-  }
+  auto launches = [&](int fused, int64_t n) -> int {
+    if (n == 0) return LBM_OK;
+    const int grid = batch_grid(variant, fused, block);
+    if (grid <= 0) return set_error(LBM_EDEVICE, "batch occupancy query failed");
+    for (int64_t s = 0; s < n; ++s) {
+      hipError_t e = launch_batch(variant, fused, jobs, hdr, (int32_t)s, block, grid, st);
+      if (e != hipSuccess) return hip_error(e, "batch launch");
+    }
+    return LBM_OK;
+  };
+  int rc = launches(plan.fused, plan.fused_launches);
+  if (rc == LBM_OK) rc = launches(1, plan.single_launches);
+  if (rc != LBM_OK) return rc;
   for (int k = 0; k < count; ++k) {
-    lbm_ctx* c = ctxs[order[k]];
-    const int64_t n = steps[order[k]];
-    c->lv[0].t += n;
-    c->lv[0].cur ^= (int)(n & 1);
-    c->t += n;
+    BatchJob J;
+    fill_job(J, ctxs[order[k]], steps[order[k]], block, 0, 0);
+    advance_job(ctxs[order[k]], J);
   }
   return LBM_OK;
 }
