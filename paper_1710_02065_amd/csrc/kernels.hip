@@ -147,7 +147,7 @@ __global__ void k_init(InitArgs a) {
     const R wr = (R)L::w(i) * (R)a.rho0;
     const T v = encode<S>(out[i], wr);
     d0[(uint64_t)i * a.pstride + c] = v;
-    d1[(uint64_t)i * a.pstride + c] = v;
+    if (d1) d1[(uint64_t)i * a.pstride + c] = v;
   }
   if (a.mask_out) a.mask_out[c] = a.mask_in ? a.mask_in[c] : kFluid;
 }

@@ -388,7 +388,7 @@ __global__ void k_minit(InitArgs a) {
 #pragma unroll
   for (int k = 0; k < NM; ++k) {
     d0[(uint64_t)k * a.pstride + c] = m[k];
-    d1[(uint64_t)k * a.pstride + c] = m[k];
+    if (d1) d1[(uint64_t)k * a.pstride + c] = m[k];
   }
 }
 

@@ -703,6 +703,12 @@ int lbm_init(lbm_ctx* ctx, int level, const double* rho, const double* u,
     if (e != hipSuccess) return hip_error(e, "hipMemsetAsync");
     ctx->status_cleared = true;
   }
+  // any level that is not a fully periodic, sponge-free, unrefined grid
+  // keeps a mask (all FLUID if none was given) with the flag bits
+  bool general = mask != nullptr || ctx->nlevels > 1 || L.chi_max > 0 ||
+                 (ctx->cfg.flags & LBM_SPONGE_FIELD);
+  for (int f = 0; f < 6; ++f)
+    if (L.face[f] != LBM_PERIODIC && L.face[f] != LBM_HALO) general = true;
   InitArgs a{};
   a.rho = rho;
   a.u = u;
@@ -710,7 +716,9 @@ int lbm_init(lbm_ctx* ctx, int level, const double* rho, const double* u,
   a.mask_in = mask;
   a.mask_out = L.mask;
   a.dst0 = L.buf[0];
-  a.dst1 = L.buf[1];
+  // the other buffer starts with the values of the cells no sweep writes
+  // (SOLID, refinement roles); without a mask every cell is written first
+  a.dst1 = general ? L.buf[1] : nullptr;
   a.ncell = (uint32_t)L.N;
   a.pstride = L.pstride;
   a.rho0 = ctx->cfg.rho0;
@@ -720,12 +728,6 @@ int lbm_init(lbm_ctx* ctx, int level, const double* rho, const double* u,
           ? launch_minit(kernel_lattice(ctx->cfg), ctx->cfg.storage, a, ctx->stream)
           : launch_init(kernel_lattice(ctx->cfg), ctx->cfg.storage, a, (uint32_t)L.N, ctx->stream);
   if (e != hipSuccess) return hip_error(e, "init launch");
-  // any level that is not a fully periodic, sponge-free, unrefined grid
-  // keeps a mask (all FLUID if none was given) with the flag bits
-  bool general = mask != nullptr || ctx->nlevels > 1 || L.chi_max > 0 ||
-                 (ctx->cfg.flags & LBM_SPONGE_FIELD);
-  for (int f = 0; f < 6; ++f)
-    if (L.face[f] != LBM_PERIODIC && L.face[f] != LBM_HALO) general = true;
   L.has_mask = general;
   if (ctx->nlevels > 1) {
     rc = refined_init_level(ctx, level, rho, u, pi_neq);
@@ -1035,7 +1037,8 @@ int lbm_set_populations(lbm_ctx* ctx, int level, const double* in) {
   PopArgs a{};
   a.native = L.buf[L.cur];
   // SOLID cells are never written by the sweep; keep both buffers equal
-  a.native2 = L.buf[L.cur ^ 1];
+  // (the other buffer: see lbm_init)
+  a.native2 = L.has_mask ? L.buf[L.cur ^ 1] : nullptr;
   a.canon = const_cast<double*>(in);
   a.ncell = (uint32_t)L.N;
   a.pstride = L.pstride;
@@ -1092,6 +1095,31 @@ int lbm_halo_buffers(lbm_ctx* ctx, int side, void** send, void** recv, size_t* b
   return LBM_OK;
 }
 
+}  // extern "C"
+
+namespace hrlbm {
+
+// Halo buffers moved by one launch: blockIdx.y is the copy.  A buffer is a
+// few hundred KB to a few MB, so a copy of its own costs a launch and its
+// latency each (5.2 us per hipMemcpyAsync of 1.3 MB, one after another; the
+// eight of a ring of four 256 x 256 slabs together 6 us).
+constexpr int kHaloCopies = 16;
+struct HaloCopies {
+  const uint4* src[kHaloCopies];
+  uint4* dst[kHaloCopies];
+  uint32_t n;  // 16-byte words of each (the buffers are padded to 256 bytes)
+};
+
+__global__ void __launch_bounds__(256) k_halo_copy(HaloCopies h) {
+  const uint4* s = h.src[blockIdx.y];
+  uint4* d = h.dst[blockIdx.y];
+  for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < h.n; i += gridDim.x * 256u) d[i] = s[i];
+}
+
+}  // namespace hrlbm
+
+extern "C" {
+
 int lbm_halo_exchange(lbm_ctx* const* ctxs, int n, int periodic) {
   if (n < 1 || !ctxs) return set_error(LBM_EINVAL, "exchange arguments");
   for (int k = 0; k < n; ++k) {
@@ -1114,17 +1142,30 @@ int lbm_halo_exchange(lbm_ctx* const* ctxs, int n, int periodic) {
   if (rc != LBM_OK) return rc;
   // subdomain k + 1 lies above k; with `periodic` subdomain 0 lies above n - 1
   const int pairs = periodic ? n : n - 1;
+  HaloCopies h{};
+  h.n = (uint32_t)((bytes + 15) / 16);
+  const uint32_t blocks = std::min<uint32_t>((h.n + 255u) / 256u, 256u);
+  uint32_t count = 0;
+  auto flush = [&]() -> int {
+    if (count == 0) return LBM_OK;
+    hipLaunchKernelGGL(k_halo_copy, dim3(blocks, count), dim3(256), 0, ctxs[0]->stream, h);
+    count = 0;
+    hipError_t e = hipGetLastError();
+    return e == hipSuccess ? LBM_OK : hip_error(e, "halo copy");
+  };
   for (int k = 0; k < pairs; ++k) {
     const Level& below = ctxs[k]->lv[0];
     const Level& above = ctxs[(k + 1) % n]->lv[0];
-    hipError_t e = hipMemcpyAsync(above.hrecv[0], below.hsend[1], bytes,
-                                  hipMemcpyDeviceToDevice, ctxs[0]->stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(below.hrecv[1], above.hsend[0], bytes, hipMemcpyDeviceToDevice,
-                         ctxs[0]->stream);
-    if (e != hipSuccess) return hip_error(e, "halo copy");
+    h.src[count] = (const uint4*)below.hsend[1];
+    h.dst[count++] = (uint4*)above.hrecv[0];
+    h.src[count] = (const uint4*)above.hsend[0];
+    h.dst[count++] = (uint4*)below.hrecv[1];
+    if (count == kHaloCopies) {
+      rc = flush();
+      if (rc != LBM_OK) return rc;
+    }
   }
-  return LBM_OK;
+  return flush();
 }
 
 void lbm_destroy(lbm_ctx* ctx) {
