@@ -3,11 +3,12 @@
 Workload (the headline): D3Q19, 256^3 periodic cells, 3D Taylor-Green
 vortex at U = 0.1 cs plus a Gaussian acoustic pulse (1e-3 rho0, sigma 8
 cells), tau = 0.52, FP32 arithmetic with FP32 population storage; synthetic
-fields generated on the host, resident in HBM before timing.  One step is one
-sweep over the whole grid (pull, moments, regularized collision, store).
+fields generated on the host, resident in HBM before timing.  One step
+updates the whole grid (pull, moments, regularized collision, store); the
+library takes two per pass over the populations.
 
 Prints one JSON line: MLUPS (whole job), the HBM roofline of the sweep kernel
-(algorithmic bytes 2 q sizeof(storage) per cell update over the kernel time
+(algorithmic bytes 2 q sizeof(storage) per cell and pass over the kernel time
 measured with HIP events on the launch stream), the other storage forms
 (FP16-shifted, FP32-shifted, FP64, and the moment storages M32 / M64 that
 keep 10 moments per cell instead of 19 populations) with their speedups, the
@@ -29,12 +30,16 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
-# workgroup size of the timed headline sweep (D3Q19 FP32), fixed so that the
-# committed kernel trace and counters describe the launch this run times
+# workgroup size of the one-step sweep of the headline grid (the timed steps
+# are taken two at a time by a kernel whose workgroups are fixed)
 HEADLINE_BLOCK = 256
+# steps the library takes per pass over the populations of these grids (even
+# counts): each pass reads and writes every population once
+STEPS_PER_PASS = 2
 METRIC = "MLUPS & % HBM roofline (D3Q19 256³); p50/p99 latency, batched serving"
 # sources each profiled kernel is compiled from
-SOURCES = {"k_sweep": ["kernels.hip", "kernels.hpp", "lattice.hpp"],
+SOURCES = {"k_sweep": ["kernels.hip", "sweep.hpp", "kernels.hpp", "lattice.hpp"],
+           "k_pair3d": ["pair3d.hip", "kernels.hpp", "lattice.hpp"],
            "k_msweep": ["msweep.hip", "kernels.hpp", "lattice.hpp"]}
 
 
@@ -350,11 +355,12 @@ def other_configs(lbm, torch, steps, shedding_steps,
         sim.block = lbm.lbm_autotune(sim.ctx, 2)
         ms = time_steps(sim, torch, steps)
         N = nx * ny
-        bytes_lup = 2 * 9 * 4 + 1
+        bytes_lup = (2 * 9 * 4 + 1) / STEPS_PER_PASS
         res["d2q9_cylinder_2048x1024_f32"] = dict(
             mlups=round(N * steps / (ms * 1e3), 1), steps=steps, workgroup=sim.block,
             hbm_gbs=round(bytes_lup * N * steps / (ms / 1e3) / 1e9, 1),
-            note="72 B/LUP populations + 1 B mask; 151 MB of state fits the 256 MB MALL")
+            note="72 B populations + 1 B mask per cell and pass of two steps; 151 MB of state "
+                 "fits the 256 MB MALL")
         del sim
         torch.cuda.empty_cache()
         # the channel in FP32 against the FP64 build (equal to the oracle within
@@ -628,11 +634,12 @@ def main():
     sim32, ms32, windows = run_gpu(lbm, torch, hs, n, args.steps, args.warmup, fields, block,
                                    windows=args.windows)
     mlups32 = N * args.steps / (ms32 * 1e3)
-    bytes_lup = 2 * (10 if moment else 19) * 4
-    per_launch_s = ms32 / 1e3 / args.steps
+    per_pass = 1 if moment else STEPS_PER_PASS
+    bytes_launch = 2 * (10 if moment else 19) * 4 * N
+    per_launch_s = ms32 / 1e3 / args.steps * per_pass
     wg32 = sim32.block
-    achieved = bytes_lup * N / per_launch_s / 1e9
-    kname = "k_msweep_d3q19_m32_256" if moment else "k_sweep_d3q19_f32_256"
+    achieved = bytes_launch / per_launch_s / 1e9
+    kname = "k_msweep_d3q19_m32_256" if moment else "k_pair3d_d3q19_f32_256"
     traffic = measured_traffic(kname) if n == 256 else None
 
     variants = {}
@@ -644,9 +651,10 @@ def main():
             log("timing %s" % st)
             sv, msv, _ = run_gpu(lbm, torch, st, n, args.steps, args.warmup, fields,
                                  HEADLINE_BLOCK if st == "f32" else 0)
-            # the moment storages move 10 values per cell each way, not 19
-            vals = 10 if st.startswith("m") else 19
-            b = 2 * vals * lbm.STORAGE_BYTES[lbm.STORAGE[st]]
+            # the moment storages move 10 values per cell each way and step,
+            # the others 19 per pass
+            vals = 10 if st.startswith("m") else 19 / STEPS_PER_PASS
+            b = round(2 * vals * lbm.STORAGE_BYTES[lbm.STORAGE[st]])
             mv = N * args.steps / (msv * 1e3)
             variants[st] = dict(value=round(mv, 1), unit="MLUPS", bytes_per_lup=b,
                                 hbm_gbs=round(b * N / (msv / 1e3 / args.steps) / 1e9, 1),
@@ -663,7 +671,8 @@ def main():
                 log("timing d3q27 %s %s" % (st, name))
                 sv, msv, _ = run_gpu(lbm, torch, st, n, max(args.steps // 4, 50),
                                      args.warmup // 4, fields, 0, lattice=27, flags=fl)
-                b = 2 * (10 if st.startswith("m") else 27) * lbm.STORAGE_BYTES[lbm.STORAGE[st]]
+                b = round(2 * (10 if st.startswith("m") else 27 / STEPS_PER_PASS) *
+                          lbm.STORAGE_BYTES[lbm.STORAGE[st]])
                 ns = max(args.steps // 4, 50)
                 order["d3q27_%s_%s" % (st, name)] = dict(
                     mlups=round(N * ns / (msv * 1e3), 1), bytes_per_lup=b,
@@ -700,9 +709,10 @@ def main():
             "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
             "traffic": traffic,
-            "algorithmic_bytes_per_launch": bytes_lup * N,
+            "algorithmic_bytes_per_launch": bytes_launch,
+            "steps_per_launch": per_pass,
             "measured_copy_gbs": copy_gbs,
-            "kernel": "k_msweep<D3Q19, float>" if moment else "k_sweep<D3Q19, f32>"},
+            "kernel": "k_msweep<D3Q19, float>" if moment else "k_pair3d<D3Q19, f32>"},
     }
     if variants:
         out["variants"] = variants

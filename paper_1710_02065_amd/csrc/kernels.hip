@@ -82,16 +82,18 @@ __device__ __forceinline__ void sweep_cell(const SweepArgs<S>& a, uint32_t c) {
 // formats (the HBM stream needs them; without the hint the general path's
 // scalar registers alone would limit it to 7), except the D3Q27 general
 // path, whose 27 pulled values need more than the 64 registers 8 waves
-// leave (7 waves, no spills), and the D3Q27 comparator collisions on either
-// path, which keep the 27 pulled values alive through the rebuild (7 waves:
-// with 64 registers the LBM-BGK sweep spilled 3.5 KB per lane); no
-// constraint for FP64.
+// leave (68: it runs at 7 waves, asked for 6, which leaves it scalar
+// registers too: 1 % faster on a refined jet), and the D3Q27 comparator
+// collisions on either path, which keep the 27 pulled values alive through
+// the rebuild (7 waves: with 64 registers the LBM-BGK sweep spilled 3.5 KB per
+// lane); no constraint for FP64.
 template <class L, class S, bool kGeneral>
 struct SweepWaves {
   static constexpr int value =
       sizeof(typename S::T) == 8
           ? 1
-          : (L::Q == 27 && (kGeneral || L::kColl != kCollRR) ? 7 : 8);
+          : L::Q != 27 ? 8
+                       : (L::kColl != kCollRR ? 7 : (kGeneral ? 6 : 8));
 };
 
 template <class L, class S, bool kGeneral, bool kNt>
@@ -361,13 +363,13 @@ __device__ __forceinline__ void batch_cell(const BatchJob& J, int32_t s, uint32_
   sweep_cell<L, S, kGeneral>(a, c);
 }
 
-// Wavefronts per SIMD of the batched sweep: those of the solo sweep, one
-// fewer on the 3D general path, where the job lookup's registers on top of
-// the sweep's made 8 (D3Q19) and 7 (D3Q27) waves spill.
+// Wavefronts per SIMD of the batched sweep: those of the solo sweep, fewer on
+// the 3D general path, where the job lookup's registers on top of the
+// sweep's made 8 (D3Q19) and 7 (D3Q27) waves spill.
 template <class L, class S, bool kGeneral>
 struct BatchWaves {
   static constexpr int value =
-      L::D == 3 && kGeneral && sizeof(typename S::T) < 8 ? SweepWaves<L, S, kGeneral>::value - 1
+      L::D == 3 && kGeneral && sizeof(typename S::T) < 8 ? (L::Q == 27 ? 6 : 7)
                                                          : SweepWaves<L, S, kGeneral>::value;
 };
 
@@ -625,14 +627,21 @@ __global__ void k_import(ImportArgs ia) {
   for (int ax = 0; ax < 3; ++ax) kc[ax] = ax < L::D ? 2 * (p[ax] - ia.lo[ax]) : 0;
   const R* M = (const R*)ia.recf;
   const R w1[3] = {(R)0.25, (R)0.5, (R)0.25};
-  const int oz = L::D == 3 ? 1 : 0;
+  // unrolled, so that the loads of a node's neighbours are in flight together
+  // (in a loop they waited for each other: 14 us for the shell of a
+  // 89 x 51 x 51 box on D3Q27 FP32)
+  constexpr int oz = L::D == 3 ? 1 : 0;
   R acc[6] = {(R)0, (R)0, (R)0, (R)0, (R)0, (R)0};
+#pragma unroll
   for (int o2 = -oz; o2 <= oz; ++o2)
+#pragma unroll
     for (int o1 = -1; o1 <= 1; ++o1)
+#pragma unroll
       for (int o0 = -1; o0 <= 1; ++o0) {
         const uint64_t c = ((uint64_t)(kc[2] + o2) * ia.fny + (uint64_t)(kc[1] + o1)) * ia.fnx +
                            (uint64_t)(kc[0] + o0);
         const R w = w1[o0 + 1] * w1[o1 + 1] * (oz ? w1[o2 + 1] : (R)1);
+#pragma unroll
         for (int q = 0; q < 6; ++q) acc[q] += w * M[c * 10 + 4 + q];
       }
   const uint64_t c0 = ((uint64_t)kc[2] * ia.fny + (uint64_t)kc[1]) * ia.fnx + (uint64_t)kc[0];
@@ -701,8 +710,10 @@ hipError_t launch_sweep(int lattice, int storage, const SweepHost& h, int block,
 #define HRLBM_DISPATCH(NAME, ARGS, FULL)                                      \
   template <class L, class S>                                                 \
   static void NAME##_t(const ARGS& a, uint32_t n, hipStream_t st) {           \
-    const uint32_t blocks = (n + 255) / 256;                                  \
-    if (blocks) hipLaunchKernelGGL((k_##NAME<L, S>), dim3(blocks), dim3(256), 0, st, a); \
+    /* few items: workgroups of one wavefront, spread over more CUs */         \
+    const uint32_t size = n < (1u << 16) ? 64u : 256u;                        \
+    const uint32_t blocks = (n + size - 1) / size;                            \
+    if (blocks) hipLaunchKernelGGL((k_##NAME<L, S>), dim3(blocks), dim3(size), 0, st, a); \
   }                                                                           \
   template <class L>                                                          \
   static void NAME##_l(int storage, const ARGS& a, uint32_t n, hipStream_t st) { \

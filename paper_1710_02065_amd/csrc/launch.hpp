@@ -262,6 +262,7 @@ struct Multi2d {
   int32_t s_off;
   int grid;
   int* query;
+  int cus;  // compute units of the device (single grid)
   hipStream_t st;
 };
 hipError_t launch_multi2d(const Multi2d& m);

@@ -16,10 +16,9 @@
 
 namespace hrlbm {
 
-template <class S, int T_, int OY_>
+template <int T_, int OX_, int OY_>
 struct Tile2 {
-  using V = typename S::T;
-  static constexpr int T = T_, OX = 64, OY = OY_, H = T - 1;
+  static constexpr int T = T_, OX = OX_, OY = OY_, H = T - 1;
   static constexpr int RX = OX + 2 * H, RY = OY + 2 * H, SLOTS = RX * RY;
   // with more than two steps, two LDS states alternate
   static constexpr int NB = T > 2 ? 2 : 1;
@@ -174,11 +173,12 @@ __device__ __forceinline__ bool plain_region(const SweepArgs<S>& a, uint32_t bx,
   return __all(plain);
 }
 
-// Rows of a tile and threads of a workgroup for T steps: the LDS of the
-// intermediate states limits the rows.
-template <int T>
+// Tile and threads of a workgroup for T steps: the LDS of the intermediate
+// states limits the rows.  Grids of few tiles are cut finer (see small_tiles).
+template <int T, bool kSmall>
 struct Shape2 {
-  static constexpr int OY = 8, NT = T == 4 ? 512 : 256;
+  using G = Tile2<T, kSmall ? 32 : 64, kSmall ? 4 : 8>;
+  static constexpr int NT = kSmall ? 384 : (T == 4 ? 512 : 256);
 };
 // Wavefronts per SIMD: what the LDS of a CU admits.
 template <class S, int T>
@@ -200,17 +200,17 @@ __device__ __forceinline__ void multi2d_any(const SweepArgs<S>& a, uint32_t bx, 
   multi2d_tile<L, S, kGeneral, G>(a, bx, by, lds, lmask, threadIdx.x, nthreads);
 }
 
-template <class L, class S, bool kGeneral, int T>
-__global__ void __launch_bounds__(Shape2<T>::NT)
+template <class L, class S, bool kGeneral, int T, bool kSmall>
+__global__ void __launch_bounds__((Shape2<T, kSmall>::NT))
     __attribute__((amdgpu_waves_per_eu(Waves2<S, T>::value)))
     k_multi2d(const SweepArgs<S> a, uint32_t tiles_x, uint32_t ntile) {
-  using G = Tile2<S, T, Shape2<T>::OY>;
+  using G = typename Shape2<T, kSmall>::G;
   __shared__ typename S::T lds[G::NB * L::Q * G::SLOTS];
   __shared__ uint8_t lmask[kGeneral ? G::SLOTS : 1];
   // each XCD takes a contiguous range of tiles
   const uint32_t k = blockIdx.x % 8u, per = ntile / 8u, rem = ntile % 8u;
   const uint32_t b = k * per + min(k, rem) + blockIdx.x / 8u;
-  multi2d_any<L, S, kGeneral, G>(a, b % tiles_x, b / tiles_x, lds, lmask, Shape2<T>::NT);
+  multi2d_any<L, S, kGeneral, G>(a, b % tiles_x, b / tiles_x, lds, lmask, Shape2<T, kSmall>::NT);
 }
 
 // ------------------------------------------------------------------------
@@ -221,11 +221,11 @@ __global__ void __launch_bounds__(Shape2<T>::NT)
 // job.
 // ------------------------------------------------------------------------
 template <class L, class S, bool kGeneral, int T>
-__global__ void __launch_bounds__(Shape2<T>::NT)
+__global__ void __launch_bounds__((Shape2<T, false>::NT))
     __attribute__((amdgpu_waves_per_eu(Waves2<S, T>::value)))
     k_batch2d(const BatchJob* __restrict__ jobs, const BatchHeader* __restrict__ hdr,
               int32_t s_off) {
-  using G = Tile2<S, T, Shape2<T>::OY>;
+  using G = typename Shape2<T, false>::G;
   constexpr uint32_t kRun = 32;
   __shared__ typename S::T lds[G::NB * L::Q * G::SLOTS];
   __shared__ uint8_t lmask[kGeneral ? G::SLOTS : 1];
@@ -253,7 +253,7 @@ __global__ void __launch_bounds__(Shape2<T>::NT)
     a.dst = (typename S::T*)J.buf[p ^ 1];
     a.t_new = J.t0 + (uint64_t)s * T + 1ull;
     const uint32_t n = tile - J.ftile_begin, tx = (J.h.nx + G::OX - 1) / G::OX;
-    multi2d_any<L, S, kGeneral, G>(a, n % tx, n / tx, lds, lmask, Shape2<T>::NT);
+    multi2d_any<L, S, kGeneral, G>(a, n % tx, n / tx, lds, lmask, Shape2<T, false>::NT);
     __syncthreads();  // LDS is rewritten by the next tile
   }
 }
@@ -272,21 +272,44 @@ int multi2d_steps(int storage, bool general, uint32_t nx, uint32_t ny, bool batc
 }
 uint32_t multi2d_tiles(uint32_t nx, uint32_t ny) { return (nx + 63) / 64 * ((ny + 7) / 8); }
 
+template <class L, class S, bool kGeneral, int T, bool kSmall>
+static hipError_t multi2d_one(const Multi2d& m) {
+  using Z = Shape2<T, kSmall>;
+  const uint32_t tx = (m.h->nx + Z::G::OX - 1) / Z::G::OX;
+  const uint32_t n = tx * ((m.h->ny + Z::G::OY - 1) / Z::G::OY);
+  hipLaunchKernelGGL((k_multi2d<L, S, kGeneral, T, kSmall>), dim3(n), dim3(Z::NT), 0, m.st,
+                     to_args_dev<S>(*m.h), tx, n);
+  return hipGetLastError();
+}
+
+// Whether a grid is stepped in the small tiles: where the large ones leave
+// CUs idle, more and smaller workgroups step fewer cells one after another;
+// past that their wider share of halo costs more.  On the general path a
+// workgroup takes several times as long, so a few large ones per CU are
+// still too uneven; FP64 pays the halo twice.  us per step, large / small:
+// periodic 128 x 128 FP64 1.98 / 1.34, FP32 1.56 / 1.15; 256 x 256 FP64 2.13 / 2.13,
+// FP32 1.64 / 1.36; 512 x 512 FP32 2.33 / 2.68; channel 300 x 200 FP32 5.7 / 3.5,
+// FP64 6.3 / 5.1; 500 x 400 FP32 6.8 / 5.3, FP64 8.4 / 9.5; 900 x 800 FP32 11.2 / 11.4.
+static bool small_tiles(const Multi2d& m) {
+  const uint32_t tiles = multi2d_tiles(m.h->nx, m.h->ny), cus = (uint32_t)m.cus;
+  const uint32_t limit = m.general ? 4 * cus : cus;
+  return tiles < (m.storage == 0 ? (m.general ? limit / 4 : limit / 2) : limit);
+}
+
 template <class L, class S, bool kGeneral, int T>
 static hipError_t multi2d_g(const Multi2d& m) {
-  const dim3 block(Shape2<T>::NT);
+  const dim3 block(Shape2<T, false>::NT);
   if (m.query)
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(m.query, k_batch2d<L, S, kGeneral, T>,
-                                                        Shape2<T>::NT, 0);
+                                                        Shape2<T, false>::NT, 0);
   if (m.jobs) {
     hipLaunchKernelGGL((k_batch2d<L, S, kGeneral, T>), dim3(m.grid), block, 0, m.st, m.jobs,
                        m.hdr, m.s_off);
-  } else {
-    const uint32_t tx = (m.h->nx + 63) / 64, n = multi2d_tiles(m.h->nx, m.h->ny);
-    hipLaunchKernelGGL((k_multi2d<L, S, kGeneral, T>), dim3(n), block, 0, m.st,
-                       to_args_dev<S>(*m.h), tx, n);
+    return hipGetLastError();
   }
-  return hipGetLastError();
+  if constexpr (T == 4)
+    if (small_tiles(m)) return multi2d_one<L, S, kGeneral, T, true>(m);
+  return multi2d_one<L, S, kGeneral, T, false>(m);
 }
 
 template <class L, class S>

@@ -483,6 +483,7 @@ static hipError_t launch_fused(const lbm_ctx* ctx, const Fused& f, int src_buf, 
     m.steps = f.steps;
     m.general = h.general;
     m.h = &h;
+    m.cus = ctx->cus;
     m.st = st;
     return launch_multi2d(m);
   }
