@@ -25,6 +25,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "kernels.hpp"
 #include "launch.hpp"
@@ -117,10 +118,11 @@ __device__ __forceinline__ typename S::R pair_collide(const typename S::T raw[L:
 }
 
 // One thread's march through output planes z0 ... z1 - 1.  x, y: the cell
-// of the first step (a lane without one takes a valid cell and drops its
-// result), slds its LDS slot; an interior thread's second step is of the
-// same cell.  Iteration `it` computes the first step of plane z0 + it + 1
-// and the second of plane z0 + it, which pulls the populations with
+// of the first step, slds its LDS slot; an interior thread's second step is of
+// the same cell.  A lane without a cell (own false) takes that of another
+// lane of its role: it writes the same values to the same slot, and its
+// stores are dropped.  Iteration `it` computes the first step of plane
+// z0 + it + 1 and the second of plane z0 + it, which pulls the populations with
 // xi_z = -1, 0, +1 from planes it + 1, it and it - 1; two warm-up iterations
 // fill what is carried.  Populations wait for their plane in LDS where it
 // has room (kUpRing, kMidRing planes), else in registers, and are written
@@ -175,9 +177,24 @@ __device__ __forceinline__ void pair_march(const PairArgs<S>& a, typename S::T* 
       raw[i] = *reinterpret_cast<const T*>(b);
     });
   };
+  // State at t + 2 of the output cell of plane offset cb; a lane without one
+  // is given an offset past the array, where the store is dropped (no lane
+  // mask around the second step: D3Q27 FP64 at 256^3 877 us a step with it,
+  // 768 without).
+  auto store_plane = [&](uint32_t off, uint32_t cb, const T v[Q]) {
+    // kNt: rows of whole 64-cell tiles are stored past the caches; of
+    // others, the line a row segment ends in is completed by the next
+    // tile or row and should meet it in L2 (250 x 131 x 97 FP32: 78 us a
+    // step with the hint, 72 without; 256^3: 255 with, 267 without)
+    T* p = a.dst;
+    static_for<0, Q>([&](auto I) {
+      store_at<kNt>(p, bytes, off, cb, v[decltype(I)::value]);
+      p = next_array(p, bytes);
+    });
+  };
+  bool bad = false;  // a density that is not positive and finite was seen
   if constexpr (G::kAhead) load_plane(-1);
-#pragma clang loop unroll(disable)
-  for (int it = -2; it < (int)(z1 - z0); ++it) {
+  auto iterate = [&](int it, auto out) {
     // (opaque to the compiler, which would otherwise hoist the 64-bit vector
     // sums of these offsets with every population's base out of the loop:
     // 103 vector registers instead of 54)
@@ -188,7 +205,7 @@ __device__ __forceinline__ void pair_march(const PairArgs<S>& a, typename S::T* 
       if constexpr (pair_needs<L, ROLE>(i)) {
         if constexpr (L::dir(i).z > 0) {
           if constexpr (G::staged(i)) {
-            if (own) row(I, G::kUpRing == 2 ? it : it - 1)[slds] = G::kUpRing == 2 ? up2[i] : up1[i];
+            row(I, G::kUpRing == 2 ? it : it - 1)[slds] = G::kUpRing == 2 ? up2[i] : up1[i];
           } else {
             up0[i] = up1[i];
           }
@@ -197,7 +214,7 @@ __device__ __forceinline__ void pair_march(const PairArgs<S>& a, typename S::T* 
           if constexpr (!G::staged(i))
             mid0[i] = mid[i];
           else if constexpr (G::kMidRing == 1)
-            if (own) row(I, it)[slds] = mid[i];
+            row(I, it)[slds] = mid[i];
         }
       }
     });
@@ -206,8 +223,7 @@ __device__ __forceinline__ void pair_march(const PairArgs<S>& a, typename S::T* 
       T post[Q];
       if constexpr (!G::kAhead) load_plane(it + 1);
       const R rho = pair_collide<L, S>(raw, a.omega1, a.rho0, post);
-      // stability watchdog: a rare, benign racy store of 1
-      if (ROLE == kInner && (!(rho > (R)0) || !(rho < (R)1e30))) a.status[0] = 1;
+      if (ROLE == kInner) bad = bad || !(rho > (R)0) || !(rho < (R)1e30);
       static_for<0, Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
         if constexpr (pair_needs<L, ROLE>(i)) {
@@ -215,13 +231,13 @@ __device__ __forceinline__ void pair_march(const PairArgs<S>& a, typename S::T* 
             up2[i] = post[i];
           } else if constexpr (L::dir(i).z == 0) {
             if constexpr (G::staged(i) && G::kMidRing == 2) {
-              if (own) row(I, it + 1)[slds] = post[i];
+              row(I, it + 1)[slds] = post[i];
             } else {
               mid[i] = post[i];
             }
           } else {
             if constexpr (G::staged(i)) {
-              if (own) row(I, it + 1)[slds] = post[i];
+              row(I, it + 1)[slds] = post[i];
             } else {
               down[i] = post[i];
             }
@@ -232,7 +248,7 @@ __device__ __forceinline__ void pair_march(const PairArgs<S>& a, typename S::T* 
     if constexpr (G::kAhead) load_plane(it + 2);
     __syncthreads();
     if constexpr (ROLE == kInner) {
-      if (own && it >= 0) {
+      if (out) {
         T raw2[Q], post[Q];
         static_for<0, Q>([&](auto I) {
           constexpr int i = decltype(I)::value;
@@ -243,21 +259,28 @@ __device__ __forceinline__ void pair_march(const PairArgs<S>& a, typename S::T* 
             raw2[i] = d.z > 0 ? up0[i] : (d.z == 0 ? mid0[i] : down[i]);
         });
         const R rho = pair_collide<L, S>(raw2, a.omega1, a.rho0, post);
-        if (!(rho > (R)0) || !(rho < (R)1e30)) a.status[0] = 1;
-        const uint32_t cb = (z0 + (uint32_t)it) * plane * kB + yb[1];
-        // kNt: rows of whole 64-cell tiles are stored past the caches; of
-        // others, the line a row segment ends in is completed by the next
-        // tile or row and should meet it in L2 (250 x 131 x 97 FP32: 78 us a
-        // step with the hint, 72 without; 256^3: 255 with, 267 without)
-        T* p = a.dst;
-        static_for<0, Q>([&](auto I) {
-          store_at<kNt>(p, bytes, xb[1], cb, post[decltype(I)::value]);
-          p = next_array(p, bytes);
-        });
+        bad = bad || !(rho > (R)0) || !(rho < (R)1e30);
+        store_plane(own ? xb[1] : bytes, (z0 + (uint32_t)it) * plane * kB + yb[1], post);
       }
     }
     __syncthreads();
+  };
+  // The two warm-up iterations, which store nothing, in a loop of their own:
+  // without the branch around the second step its LDS reads and the next
+  // plane's loads mix freely (256^3, us per step, branch / two loops: D3Q27
+  // FP32 374 / 365, FP16S 277 / 254; 64^3 D3Q19 FP32 6.7 / 6.3).  FP64 keeps
+  // the branch: at its 168 registers two loops spill (D3Q27 768 / 798).
+  if constexpr (sizeof(T) == 8) {
+#pragma clang loop unroll(disable)
+    for (int it = -2; it < (int)(z1 - z0); ++it) iterate(it, it >= 0);
+  } else {
+#pragma clang loop unroll(disable)
+    for (int it = -2; it < 0; ++it) iterate(it, std::false_type{});
+#pragma clang loop unroll(disable)
+    for (int it = 0; it < (int)(z1 - z0); ++it) iterate(it, std::true_type{});
   }
+  // stability watchdog: a rare, benign racy store of 1
+  if (ROLE == kInner && bad) a.status[0] = 1;
 }
 
 template <class L, class S, bool kNt>
@@ -373,7 +396,7 @@ static double iteration_us(int q, int storage) {
 // 128 x 64 x 24 6 / 7, 12 x 200 x 64 8 / 14 (lanes of narrow rows idle);
 // FP16S 256^3 225 / 175, 250 x 131 x 97 47 / 36, 200 x 150 x 130 56 / 67
 // (a quarter of the lanes idle, and the 2-byte pass is bound by its
-// arithmetic); D3Q27 FP32 256^3 642 / 367; FP64 256^3 D3Q19 928 / 500.
+// arithmetic); D3Q27 FP32 256^3 642 / 365; FP64 256^3 D3Q19 928 / 500.
 uint32_t pair3d_planes(int q, int storage, uint32_t nx, uint32_t ny, uint32_t nz, uint32_t cus) {
   if (cus == 0) return 0;
   const uint64_t slots = storage == 3 ? 2ull * cus : cus;
