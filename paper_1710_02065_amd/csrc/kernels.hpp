@@ -330,8 +330,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 // costs one even and one odd sum.  Every coefficient is multiplied by the
 // smallest weight first, which leaves the populations of that weight without
 // a multiplication and the others with an exact one (the weights of a
-// lattice differ by powers of two).  The odd part is a sum over the axes,
-// 3 xi_a T_a(xi_b^2, xi_c^2), with
+// lattice differ by powers of two, but for the 1/3 of D3Q19, below).  The odd
+// part is a sum over the axes, 3 xi_a T_a(xi_b^2, xi_c^2), with
 //   T_a = m1_a + (xi_b^2 - cs^2) A_abb / 3 + (xi_c^2 - cs^2) A_acc / 3
 // shared by all directions with the same squares, plus the xyz term where
 // the lattice carries it: D3Q19 needs 30 operations for the three T_a and one
@@ -351,8 +351,20 @@ __device__ __forceinline__ void rebuild_all(const Coeffs<L, R>& c, R base, R out
 #pragma unroll
   for (int a = 0; a < 3; ++a) t1[a] = (R)we * c.m1[a];
   const R tr = m2[0] + m2[1] + (L::D == 3 ? m2[2] : (R)0);
-  // even part at xi = 0: m0 - cs^2 tr / (2 cs^4) = m0 - 1.5 tr
-  const R e0 = (R)we * (base + c.m0) - (R)1.5 * tr;
+  // even part at xi = 0: m0 - cs^2 tr / (2 cs^4) = m0 - 1.5 tr.  D3Q19's rest
+  // weight is 12 times the smallest, and 12 we is not the rounded 1/3 that
+  // stored_moments takes off: with `base` inside that factor every step added
+  // their difference to the mass (p' after 5000 steps 5e-2 off the FP64 run
+  // at 256^3, 1.4e-4 now).  `base` joins each sum last instead, which also
+  // spares m0 the rounding of base + m0.
+  constexpr bool kBaseLast = L::Q != 27;
+  R e0, er;
+  if constexpr (kBaseLast) {
+    er = (R)we * c.m0 - (R)1.5 * tr;
+    e0 = (R)we * base + er;
+  } else {
+    e0 = er = (R)we * (base + c.m0) - (R)1.5 * tr;
+  }
   // third-order coefficients A_abb, A_acc over their norms: (xyy, xzz),
   // (xxy, yzz), (xxz, yyz); D3Q19 resolves their sum and difference only
   constexpr int kA[3][2] = {{kXYY, kXZZ}, {kXXY, kYZZ}, {kXXZ, kYYZ}};
@@ -394,14 +406,15 @@ __device__ __forceinline__ void rebuild_all(const Coeffs<L, R>& c, R base, R out
     constexpr int k = decltype(KK)::value;
     mh[k] = (R)(high_order(L::high(k)) % 2 == 0 ? we : we / 3.0) * c.mh[k];
   });
-  {
-    R h0 = e0;
-    static_for<0, L::KH>([&](auto KK) {
-      constexpr double hk = high_h<L>(0, decltype(KK)::value);
-      if constexpr (hk != 0.0) h0 += (R)hk * mh[decltype(KK)::value];
-    });
-    out[0] = (R)(L::w(0) / we) * h0;
-  }
+  static_for<0, L::KH>([&](auto KK) {
+    constexpr double hk = high_h<L>(0, decltype(KK)::value);
+    if constexpr (hk != 0.0) er += (R)hk * mh[decltype(KK)::value];
+  });
+  er = (R)(L::w(0) / we) * er;
+  if constexpr (kBaseLast)
+    out[0] = (R)L::w(0) * base + er;
+  else
+    out[0] = er;
   static_for<0, (L::Q - 1) / 2>([&](auto K) {
     constexpr int i = 1 + 2 * decltype(K)::value;
     constexpr Dir v = L::dir(i);

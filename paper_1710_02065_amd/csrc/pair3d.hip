@@ -15,7 +15,7 @@
 // 252 (66.6k MLUPS; of its 660 + 512 populations' traffic per 1024 updates
 // 5.8 TB/s, so HBM still bounds it), FP16S 225 / 175 (bound by its
 // arithmetic: 8 x 390 + 3 x 185 vector instructions per plane of a tile),
-// FP64 928 / 500; D3Q27 FP32 642 / 367, FP16S 315 / 275, FP64 1317 / 866.
+// FP64 928 / 508; D3Q27 FP32 642 / 365, FP16S 315 / 254, FP64 1317 / 768.
 // Tried on the way: populations waiting for their plane in registers instead
 // of LDS (103 vector registers, one workgroup less per CU), 4, 6, 7 and 12
 // rows per tile (266, 338, 311, 287 us at their best chunk length against
@@ -396,7 +396,7 @@ static double iteration_us(int q, int storage) {
 // 128 x 64 x 24 6 / 7, 12 x 200 x 64 8 / 14 (lanes of narrow rows idle);
 // FP16S 256^3 225 / 175, 250 x 131 x 97 47 / 36, 200 x 150 x 130 56 / 67
 // (a quarter of the lanes idle, and the 2-byte pass is bound by its
-// arithmetic); D3Q27 FP32 256^3 642 / 365; FP64 256^3 D3Q19 928 / 500.
+// arithmetic); D3Q27 FP32 256^3 642 / 365; FP64 256^3 D3Q19 928 / 508.
 uint32_t pair3d_planes(int q, int storage, uint32_t nx, uint32_t ny, uint32_t nz, uint32_t cus) {
   if (cus == 0) return 0;
   const uint64_t slots = storage == 3 ? 2ull * cus : cus;

@@ -1103,7 +1103,7 @@ namespace hrlbm {
 // Halo buffers moved by one launch: blockIdx.y is the copy.  A buffer is a
 // few hundred KB to a few MB, so a copy of its own costs a launch and its
 // latency each (5.2 us per hipMemcpyAsync of 1.3 MB, one after another; the
-// eight of a ring of four 256 x 256 slabs together 6 us).
+// eight of a ring of four 256 x 256 slabs together 6.3 us).
 constexpr int kHaloCopies = 16;
 struct HaloCopies {
   const uint4* src[kHaloCopies];
