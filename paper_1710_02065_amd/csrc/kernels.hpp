@@ -944,7 +944,11 @@ __device__ __forceinline__ R sponge_chi(const int32_t* width, R chi_max,
     const R s = (f & 1) ? (R)pos[a] : (R)(n[a] - 1u - pos[a]);
     const R s0 = (R)(int64_t)(n[a] - (uint32_t)W);
     if (s < s0) continue;
-    const R d = (s - s0) * ((R)1 / (R)W);
+    // (s - s0) / W, correctly rounded, from the width's rounded reciprocal (the
+    // same for every cell) by the remainder step of Markstein, IBM J. Res. Dev.
+    // 34, 111 (1990): the last cells' 1 - d magnifies an error of d by W
+    const R iw = (R)1 / (R)W, q = (s - s0) * iw;
+    const R d = fused(fused(-q, (R)W, s - s0), iw, q);
     const R sig = (R)(3125.0 / 256.0) * ((R)1 - d) * (d * d) * (d * d);
     best = sig > best ? sig : best;
   }

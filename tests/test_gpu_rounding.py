@@ -51,3 +51,29 @@ def errors(q, full, storage):
 def test_fp32_error_stays_below_the_recorded_one(q, full):
     e_rho, e_u = errors(q, full, "f32")
     assert e_rho <= FP32_BARS[q, full][0] and e_u <= FP32_BARS[q, full][1], (e_rho, e_u)
+
+
+@pytest.mark.parametrize("width", [3, 49, 103, 197, 321])
+def test_fp32_layer_strength_is_of_the_correctly_rounded_distance(width):
+    """One step from rest with a moving reference state: the momentum of a cell
+    in the layer gives its strength chi.  With d = (s - s0) / W rounded once,
+    the rest of chi and the collision is about 30 roundings; d a rounding
+    further off changes 1 - d, and with it chi, by W roundings in the
+    outermost cells.  (Storage of deviations: a population that carries its
+    rest part has no digits for the small momenta.)"""
+    from paper_1710_02065_amd import lbm
+    nx, U, chi_max = width + 7, 0.1, 0.2
+    sim = lbm.Simulation(lattice=9, shape=(nx, 6, 1), storage="f32s", tau=0.6,
+                         face_bc=(2, 2, 0, 0, 0, 0), sponge_width=(0, width, 0, 0, 0, 0),
+                         chi_max=chi_max, rho_ref=1.0, u_ref=(U, 0.0, 0.0))
+    f = sim.init().step(1).populations().cpu().numpy().reshape(9, 6, nx)
+    xi, _ = lbm.lbm_lattice_table(9)
+    j = np.tensordot(xi[:, 0].astype(float), f, 1)[3]
+    s = np.arange(nx) - (nx - width)
+    d = np.maximum(s.astype(np.float32) / np.float32(width), 0).astype(np.float64)
+    chi = chi_max * 3125 / 256 * (1 - d) * d ** 4
+    want = (1 - chi) * 0.5 * chi * U / (1 + 0.5 * chi) + chi * U
+    inside = want > 0
+    assert inside.sum() == width - 1
+    assert np.abs(j[inside] / want[inside] - 1).max() <= 32 * 2.0 ** -24
+    assert np.abs(j[~inside]).max() <= 1e-13
