@@ -232,6 +232,11 @@ int lbm_init(lbm_ctx* ctx, int level, const double* rho, const double* u,
  * flag reported by lbm_sync / lbm_moments. */
 int lbm_step(lbm_ctx* ctx, int64_t n);
 
+/* Steps lbm_step takes in one pass over the grid: 1, 2 or 4 (what is left of a
+ * count is taken in passes of two or one).  Fixed by the grid, its faces and
+ * its mask from lbm_init on; negative before. */
+int lbm_steps_per_pass(const lbm_ctx* ctx);
+
 /* Wait for the context's stream; return LBM_OK or the sticky
  * LBM_EUNSTABLE / LBM_EDEVICE. */
 int lbm_sync(lbm_ctx* ctx);

@@ -397,19 +397,23 @@ static double iteration_us(int q, int storage) {
 // FP16S 256^3 225 / 175, 250 x 131 x 97 47 / 36, 200 x 150 x 130 56 / 67
 // (a quarter of the lanes idle, and the 2-byte pass is bound by its
 // arithmetic); D3Q27 FP32 256^3 642 / 365; FP64 256^3 D3Q19 928 / 508.
+// The search takes the rounds r in which a CU works off its workgroups, and the
+// most chunks that fit them; r rounds take at least 2 r iterations more than
+// the cells alone, which ends it after few (10^6 planes of 4 x 4 cells: two).
 uint32_t pair3d_planes(int q, int storage, uint32_t nx, uint32_t ny, uint32_t nz, uint32_t cus) {
   if (cus == 0) return 0;
   const uint64_t slots = storage == 3 ? 2ull * cus : cus;
   const uint64_t ntile = (uint64_t)((nx + 63) / 64) * ((ny + 7) / 8);
   uint32_t best = nz;
-  uint64_t iterations = ~0ull;
-  for (uint32_t ch = 1; ch <= nz; ++ch) {
-    const uint32_t zc = (nz + ch - 1) / ch;
-    const uint64_t wg = ntile * ((nz + zc - 1) / zc);
-    const uint64_t n = (wg + slots - 1) / slots * (zc + 2);
+  uint64_t iterations = ~0ull, chunks = 0;
+  for (uint64_t r = (ntile + slots - 1) / slots;
+       chunks < nz && (iterations == ~0ull || ntile * nz + 2 * r * slots < iterations * slots); ++r) {
+    chunks = std::min<uint64_t>(nz, r * slots / ntile);
+    const uint64_t zc = (nz + chunks - 1) / chunks;
+    const uint64_t n = r * (zc + 2);
     if (n < iterations) {
       iterations = n;
-      best = zc;
+      best = (uint32_t)zc;
     }
   }
   const double bytes = 2.0 * q * (storage == 0 ? 8 : storage == 3 ? 2 : 4) * nx * ny * nz;

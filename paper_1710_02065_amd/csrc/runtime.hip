@@ -448,13 +448,6 @@ int sweep_level(lbm_ctx* ctx, int l, hipStream_t st) {
   return LBM_OK;
 }
 
-// Steps of level 0 taken in one pass (1: one-step sweeps), and the planes per
-// workgroup of the 3D pass.
-struct Fused {
-  int steps = 1;
-  uint32_t zc = 0;
-};
-
 static Fused fused_steps(const lbm_ctx* ctx) {
   const lbm_config& c = ctx->cfg;
   Fused f;
@@ -492,7 +485,7 @@ static hipError_t launch_fused(const lbm_ctx* ctx, const Fused& f, int src_buf, 
 
 // Enqueue n single-grid steps eagerly.
 static int step_eager(lbm_ctx* ctx, int64_t n, hipStream_t st) {
-  Fused f = n > 1 ? fused_steps(ctx) : Fused{};
+  Fused f = ctx->fused;
   while (f.steps > 1 && n > 1) {
     // (what is left of a pass of four steps: one of two, then a single step)
     if (n < f.steps) f.steps = 2;
@@ -607,7 +600,7 @@ static int step_graph(lbm_ctx* ctx, int64_t chunks, hipStream_t st) {
     hipError_t e = hipStreamBeginCapture(ctx->capture_stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_error(e, "hipStreamBeginCapture");
     int buf = L.cur;
-    const Fused f = fused_steps(ctx);
+    const Fused f = ctx->fused;
     for (int64_t s = 0; f.steps > 1 && s < kGraphSteps && e == hipSuccess; s += f.steps) {
       e = launch_fused(ctx, f, buf, (uint64_t)(L.t + 1 + s), ctx->capture_stream);
       buf ^= 1;
@@ -730,6 +723,7 @@ int lbm_init(lbm_ctx* ctx, int level, const double* rho, const double* u,
           : launch_init(kernel_lattice(ctx->cfg), ctx->cfg.storage, a, (uint32_t)L.N, ctx->stream);
   if (e != hipSuccess) return hip_error(e, "init launch");
   L.has_mask = general;
+  ctx->fused = fused_steps(ctx);
   if (ctx->nlevels > 1) {
     rc = refined_init_level(ctx, level, rho, u, pi_neq);
     if (rc != LBM_OK) return rc;
@@ -812,6 +806,11 @@ int lbm_sync(lbm_ctx* ctx) {
   if (ctx->unstable)
     return set_error(LBM_EUNSTABLE, "non-finite or non-positive density seen");
   return LBM_OK;
+}
+
+int lbm_steps_per_pass(const lbm_ctx* ctx) {
+  int rc = check_ready(ctx);
+  return rc != LBM_OK ? rc : ctx->fused.steps;
 }
 
 int64_t lbm_time(const lbm_ctx* ctx) { return ctx ? ctx->t : -1; }

@@ -46,6 +46,14 @@ struct GraphEntry {
   hipGraphExec_t exec = nullptr;
 };
 
+// Steps of level 0 taken in one pass (1: one-step sweeps), and the planes per
+// workgroup of the 3D pass.  Fixed by the grid and its mask: chosen once, when
+// the grid is initialised.
+struct Fused {
+  int steps = 1;
+  uint32_t zc = 0;
+};
+
 struct Refinement;  // two-level coupling state (refine.hip)
 
 }  // namespace hrlbm
@@ -74,6 +82,7 @@ struct lbm_ctx {
   bool has_inlet = false;
   int64_t t = 0;
   int block = 256;
+  hrlbm::Fused fused;
   std::map<int, hrlbm::GraphEntry> graphs;
   // interface l couples level l (parent) and level l + 1 (child)
   hrlbm::Refinement* ref[hrlbm::kMaxLevels - 1] = {};

@@ -32,7 +32,8 @@ STORAGE_BYTES = {LBM_F64: 8, LBM_F32: 4, LBM_F32S: 4, LBM_F16S: 2, LBM_M64: 8, L
 
 # every symbol the header declares
 EXPORTS = ["lbm_config_init", "lbm_required_bytes", "lbm_create", "lbm_bind_memory",
-           "lbm_init", "lbm_step", "lbm_sync", "lbm_time", "lbm_updates_per_step",
+           "lbm_init", "lbm_step", "lbm_steps_per_pass", "lbm_sync", "lbm_time",
+           "lbm_updates_per_step",
            "lbm_level_shape",
            "lbm_moments", "lbm_probe", "lbm_accumulate", "lbm_force", "lbm_totals", "lbm_set_sponge",
            "lbm_get_populations", "lbm_set_populations", "lbm_set_time", "lbm_interface_bytes",
@@ -85,6 +86,7 @@ def lib():
         L.lbm_bind_memory.argtypes = [vp, vp, C.c_size_t]
         L.lbm_init.argtypes = [vp, C.c_int, dp, dp, dp, vp]
         L.lbm_step.argtypes = [vp, i64]
+        L.lbm_steps_per_pass.argtypes = [vp]
         L.lbm_sync.argtypes = [vp]
         L.lbm_time.argtypes = [vp]
         L.lbm_time.restype = i64
@@ -157,6 +159,10 @@ def lbm_init(ctx, level, rho=None, u=None, pi_neq=None, mask=None):
 
 def lbm_step(ctx, n):
     return _check(lib().lbm_step(ctx, int(n)))
+
+
+def lbm_steps_per_pass(ctx):
+    return _check(lib().lbm_steps_per_pass(ctx))
 
 
 def lbm_sync(ctx):
@@ -373,6 +379,10 @@ class Simulation:
     def step(self, n=1):
         lbm_step(self.ctx, n)
         return self
+
+    @property
+    def steps_per_pass(self):
+        return lbm_steps_per_pass(self.ctx)
 
     def sync(self):
         return lbm_sync(self.ctx)
