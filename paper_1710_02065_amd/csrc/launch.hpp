@@ -266,9 +266,19 @@ struct Multi2d {
   hipStream_t st;
 };
 hipError_t launch_multi2d(const Multi2d& m);
-// steps per pass (1: one-step sweeps) and tiles of a grid
-int multi2d_steps(int storage, bool general, uint32_t nx, uint32_t ny, bool batch);
+// steps per pass of a single grid on a device with `cus` compute units (1:
+// one-step sweeps), whether two left over are taken in a pass, and (large) tiles
+int multi2d_steps(int storage, bool general, uint32_t nx, uint32_t ny, uint32_t cus);
+bool multi2d_two(int storage, bool general, uint32_t nx, uint32_t ny);
 uint32_t multi2d_tiles(uint32_t nx, uint32_t ny);
+int batch2d_steps(int storage, bool general);  // of a pass of a batch
+// expected times in microseconds of a launch and of a grid's cells in it at full
+// load: a single step of a grid or of a batch's job, and a batch's pass
+struct Time2d {
+  double launch, cells;
+};
+Time2d step2d_time(int storage, bool general, bool batch, uint32_t nx, uint32_t ny);
+Time2d batch2d_time(int storage, bool general, uint32_t nx, uint32_t ny);
 // persistent batched sweep: grid of `grid` workgroups of `block` threads
 // variant = lattice code * 16 + storage * 2 + (general path ? 1 : 0)
 // s_off: offset added to the device-side step index for this launch

@@ -11,6 +11,8 @@
 // FP32: 174k MLUPS, about 3.6 TB/s; one-step sweep 82k at 5.9 TB/s).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <cstdint>
 
 #include "kernels.hpp"
@@ -279,28 +281,67 @@ __global__ void __launch_bounds__((Shape2<T, false>::NT))
   }
 }
 
-// Steps per pass.  A batch takes four at a time, but two on the general path
-// of the 4- and 8-byte storages, whose larger halo costs more there than the
-// second pass it saves; a single grid takes four on that path too while its
-// tiles do not fill the device.  us per step, one at a time / two / four:
-// periodic 4000 x 3001 FP32 147 / 90 / 75, FP16S 79 / 58 / 51, 128 x 128
-// FP64 3.2 / 2.8 / 2.0; cylinder channel 2048 x 1024 FP32 32 / 18 / 21,
-// FP16S 26 / 20 / 19, FP64 60 / 38 / 44; 1000 x 700 FP32 14.4 / 13.9 / 11.9.
-int multi2d_steps(int storage, bool general, uint32_t nx, uint32_t ny, bool batch) {
-  if (nx < 4 || ny < 4) return 1;  // the halo wraps once
-  if (!general || storage == 3) return 4;
-  return !batch && (uint64_t)nx * ny < (1u << 20) ? 4 : 2;
-}
-uint32_t multi2d_tiles(uint32_t nx, uint32_t ny) { return (nx + 63) / 64 * ((ny + 7) / 8); }
+// Estimated times in microseconds: of a launch whatever it covers, and of its
+// tiles (a step: cells) at full load.  A tile costs the same however few
+// cells it holds, so a narrow grid pays for lanes that idle, and on the
+// general path a tile at an edge of the grid costs up to twice one inside
+// it.  Fitted to 64 steps on single grids of 3000 to 12 million cells, 4 to 260
+// cells wide, 4 to 40 high or of any side ratio from 0.35 to 3, and on batches of
+// 1 to 12 grids of 9000 to 5 million cells together, to 4-20 % (r.m.s.).
+struct Fit2d {
+  double launch;
+  double inside, edge;  // per 1000 tiles (a step: per 1000 cells, per 1000 ends of rows)
+};
+// periodic and general path; storages of 8, 4 and 2 bytes
+constexpr Fit2d kStepFit[2][3] = {{{2.9, 0.0263, 0.0}, {2.8, 0.0127, 0.0}, {2.8, 0.0066, 0.0}},
+                                  {{4.3, 0.0256, 0.003}, {4.5, 0.0125, 0.049}, {5.2, 0.0080, 0.177}}};
+constexpr Fit2d kBatchStepFit[2][3] = {
+    {{3.3, 0.0273, 0.0}, {3.3, 0.0134, 0.0}, {3.5, 0.0070, 0.0}},
+    {{5.4, 0.0282, 0.0}, {5.8, 0.0139, 0.099}, {5.8, 0.0105, 0.134}}};
+// a batch's pass (two steps on the general path of the 8- and 4-byte storages,
+// else four)
+constexpr Fit2d kBatchPassFit[2][3] = {{{8.9, 27.0, 23.4}, {7.9, 12.1, 11.8}, {7.5, 9.9, 10.0}},
+                                       {{14.2, 17.1, 20.3}, {13.4, 10.0, 12.4}, {19.1, 20.5, 28.6}}};
+// a single grid's: two steps, four in the large tiles, four in the small ones
+constexpr Fit2d kPassFit[2][3][3] = {
+    {{{5.2, 13.2, 9.1}, {6.7, 25.1, 23.1}, {4.4, 11.2, 11.2}},
+     {{4.7, 6.6, 4.4}, {5.9, 10.7, 9.9}, {4.6, 3.1, 3.1}},
+     {{4.9, 3.5, 3.1}, {6.2, 6.7, 7.0}, {4.5, 2.7, 3.0}}},
+    {{{13.2, 14.5, 18.6}, {18.8, 34.8, 61.0}, {9.9, 14.6, 26.9}},
+     {{12.9, 7.2, 10.1}, {18.0, 15.6, 30.5}, {9.7, 5.7, 11.6}},
+     {{14.0, 5.3, 10.0}, {19.2, 11.9, 24.2}, {10.0, 5.3, 11.8}}}};
+static int fit_row(int storage) { return storage == 0 ? 0 : storage == 3 ? 2 : 1; }
 
-template <class L, class S, bool kGeneral, int T, bool kSmall>
-static hipError_t multi2d_one(const Multi2d& m) {
-  using Z = Shape2<T, kSmall>;
-  const uint32_t tx = (m.h->nx + Z::G::OX - 1) / Z::G::OX;
-  const uint32_t n = tx * ((m.h->ny + Z::G::OY - 1) / Z::G::OY);
-  hipLaunchKernelGGL((k_multi2d<L, S, kGeneral, T, kSmall>), dim3(n), dim3(Z::NT), 0, m.st,
-                     to_args_dev<S>(*m.h), tx, n);
-  return hipGetLastError();
+Time2d step2d_time(int storage, bool general, bool batch, uint32_t nx, uint32_t ny) {
+  const Fit2d& f = (batch ? kBatchStepFit : kStepFit)[general][fit_row(storage)];
+  const double cells = (double)nx * ny, ends = 2.0 * std::min((double)ny, cells / 64.0);
+  return Time2d{f.launch, 1e-3 * (f.inside * cells + f.edge * ends)};
+}
+
+// Tiles of a row (or column) of n cells that are whole and have T cells beside
+// them (see inside()).
+static double inside_tiles(uint32_t n, uint32_t tile, uint32_t T) {
+  const uint32_t first = (T + tile - 1) / tile;
+  return n < first * tile + tile + T ? 0.0 : (double)((n - tile - T) / tile - first + 1);
+}
+
+// Of a pass of `steps` in tiles of ox x oy cells.
+static Time2d tiles_time(const Fit2d& f, uint32_t nx, uint32_t ny, uint32_t steps, uint32_t ox,
+                         uint32_t oy) {
+  const double all = std::ceil((double)nx / ox) * std::ceil((double)ny / oy);
+  const double in = inside_tiles(nx, ox, steps) * inside_tiles(ny, oy, steps);
+  return Time2d{f.launch, 1e-3 * (f.inside * in + f.edge * (all - in))};
+}
+
+Time2d batch2d_time(int storage, bool general, uint32_t nx, uint32_t ny) {
+  return tiles_time(kBatchPassFit[general][fit_row(storage)], nx, ny,
+                    (uint32_t)batch2d_steps(storage, general), 64, 8);
+}
+
+static Time2d pass2d_time(int storage, bool general, uint32_t nx, uint32_t ny, int steps,
+                          bool small) {
+  const Fit2d& f = kPassFit[general][fit_row(storage)][steps == 2 ? 0 : small ? 2 : 1];
+  return tiles_time(f, nx, ny, (uint32_t)steps, small ? 32 : 64, small ? 4 : 8);
 }
 
 // Whether a grid is stepped in the small tiles: where the large ones leave
@@ -311,10 +352,59 @@ static hipError_t multi2d_one(const Multi2d& m) {
 // periodic 128 x 128 FP64 1.98 / 1.34, FP32 1.56 / 1.15; 256 x 256 FP64 2.13 / 2.13,
 // FP32 1.64 / 1.36; 512 x 512 FP32 2.33 / 2.68; channel 300 x 200 FP32 5.7 / 3.5,
 // FP64 6.3 / 5.1; 500 x 400 FP32 6.8 / 5.3, FP64 8.4 / 9.5; 900 x 800 FP32 11.2 / 11.4.
-static bool small_tiles(const Multi2d& m) {
-  const uint32_t tiles = multi2d_tiles(m.h->nx, m.h->ny), cus = (uint32_t)m.cus;
-  const uint32_t limit = m.general ? 4 * cus : cus;
-  return tiles < (m.storage == 0 ? (m.general ? limit / 4 : limit / 2) : limit);
+static bool small_tiles(int storage, bool general, uint32_t nx, uint32_t ny, uint32_t cus) {
+  const uint32_t tiles = multi2d_tiles(nx, ny);
+  const uint32_t limit = general ? 4 * cus : cus;
+  return tiles < (storage == 0 ? (general ? limit / 4 : limit / 2) : limit);
+}
+
+// Whether a pass is taken in place of single steps: where it is expected to
+// take under 0.85 of their time, which covers the fit's error (of 366 grids
+// measured four had a pass that was slower, by 2 to 6 %).  us per step, one at a
+// time / in the pass a rule without the times took: periodic 8 x 112500 FP32
+// 14.8 / 33.4, 8 x 3750 FP64 3.1 / 3.6; channel 32 x 28125 FP32 18.2 / 36.1, 96 x 41666 FP64
+// 107 / 118, 130 x 30769 FP16S 51 / 73, 332 x 332 FP64 6.2 / 6.8.
+static bool pays(const Time2d& pass, const Time2d& step, int steps) {
+  return pass.launch + pass.cells < 0.85 * steps * (step.launch + step.cells);
+}
+
+// Steps per pass of a single grid: four, but two on the general path of the
+// 4- and 8-byte storages, whose larger halo costs more there than the second
+// pass it saves, once the tiles fill the device; one where that does not pay.
+// us per step, one at a time / two / four: periodic 4000 x 3001 FP32 147 / 90 / 69,
+// FP16S 79 / 58 / 49, 128 x 128 FP64 3.2 / 2.8 / 1.3; cylinder channel
+// 2048 x 1024 FP32 32 / 18 / 21, FP16S 26 / 20 / 19, FP64 60 / 38 / 44; 1000 x 700 FP32
+// 14.4 / 13.9 / 11.9.
+int multi2d_steps(int storage, bool general, uint32_t nx, uint32_t ny, uint32_t cus) {
+  if (nx < 4 || ny < 4) return 1;  // the halo wraps once
+  const int steps = !general || storage == 3 || (uint64_t)nx * ny < (1u << 20) ? 4 : 2;
+  const bool small = steps == 4 && small_tiles(storage, general, nx, ny, cus);
+  return pays(pass2d_time(storage, general, nx, ny, steps, small),
+              step2d_time(storage, general, false, nx, ny), steps)
+             ? steps
+             : 1;
+}
+
+// Whether two steps left over by passes of four are taken in one.
+bool multi2d_two(int storage, bool general, uint32_t nx, uint32_t ny) {
+  return nx >= 4 && ny >= 4 &&
+         pays(pass2d_time(storage, general, nx, ny, 2, false),
+              step2d_time(storage, general, false, nx, ny), 2);
+}
+
+// Steps per pass of a batch: as of a single grid whose tiles fill the device.
+int batch2d_steps(int storage, bool general) { return !general || storage == 3 ? 4 : 2; }
+
+uint32_t multi2d_tiles(uint32_t nx, uint32_t ny) { return (nx + 63) / 64 * ((ny + 7) / 8); }
+
+template <class L, class S, bool kGeneral, int T, bool kSmall>
+static hipError_t multi2d_one(const Multi2d& m) {
+  using Z = Shape2<T, kSmall>;
+  const uint32_t tx = (m.h->nx + Z::G::OX - 1) / Z::G::OX;
+  const uint32_t n = tx * ((m.h->ny + Z::G::OY - 1) / Z::G::OY);
+  hipLaunchKernelGGL((k_multi2d<L, S, kGeneral, T, kSmall>), dim3(n), dim3(Z::NT), 0, m.st,
+                     to_args_dev<S>(*m.h), tx, n);
+  return hipGetLastError();
 }
 
 template <class L, class S, bool kGeneral, int T>
@@ -329,7 +419,8 @@ static hipError_t multi2d_g(const Multi2d& m) {
     return hipGetLastError();
   }
   if constexpr (T == 4)
-    if (small_tiles(m)) return multi2d_one<L, S, kGeneral, T, true>(m);
+    if (small_tiles(m.storage, m.general, m.h->nx, m.h->ny, (uint32_t)m.cus))
+      return multi2d_one<L, S, kGeneral, T, true>(m);
   return multi2d_one<L, S, kGeneral, T, false>(m);
 }
 

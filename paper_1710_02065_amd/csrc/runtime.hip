@@ -456,7 +456,9 @@ static Fused fused_steps(const lbm_ctx* ctx) {
     return f;
   const bool general = sweep_args(ctx, 0, 0, 0).general;
   if (c.lattice == LBM_D2Q9) {
-    f.steps = multi2d_steps(c.storage, general, (uint32_t)c.nx, (uint32_t)c.ny, false);
+    f.steps = multi2d_steps(c.storage, general, (uint32_t)c.nx, (uint32_t)c.ny,
+                            (uint32_t)ctx->cus);
+    if (f.steps == 4 && multi2d_two(c.storage, general, (uint32_t)c.nx, (uint32_t)c.ny)) f.rest = 2;
   } else if (!general) {
     f.zc = pair3d_planes(c.lattice, c.storage, (uint32_t)c.nx, (uint32_t)c.ny, (uint32_t)c.nz,
                          (uint32_t)ctx->cus);
@@ -487,8 +489,9 @@ static hipError_t launch_fused(const lbm_ctx* ctx, const Fused& f, int src_buf, 
 static int step_eager(lbm_ctx* ctx, int64_t n, hipStream_t st) {
   Fused f = ctx->fused;
   while (f.steps > 1 && n > 1) {
-    // (what is left of a pass of four steps: one of two, then a single step)
-    if (n < f.steps) f.steps = 2;
+    // (what is left of a pass of four steps: one of two, then single steps)
+    if (n < f.steps) f.steps = f.rest;
+    if (f.steps == 1) break;
     n -= f.steps;
     Level& L = ctx->lv[0];
     hipError_t e = launch_fused(ctx, f, L.cur, (uint64_t)(L.t + 1), st);

@@ -46,11 +46,11 @@ struct GraphEntry {
   hipGraphExec_t exec = nullptr;
 };
 
-// Steps of level 0 taken in one pass (1: one-step sweeps), and the planes per
-// workgroup of the 3D pass.  Fixed by the grid and its mask: chosen once, when
+// Steps of level 0 taken in one pass (1: one-step sweeps), in a pass of what is
+// left over (2 or 1), and the planes per workgroup of the 3D pass.  Fixed by the grid and its mask: chosen once, when
 // the grid is initialised.
 struct Fused {
-  int steps = 1;
+  int steps = 1, rest = 1;
   uint32_t zc = 0;
 };
 

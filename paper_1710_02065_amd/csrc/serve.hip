@@ -162,16 +162,56 @@ static int batch_variant(const lbm_ctx* c) {
   return sweep_lattice(c->cfg) * 16 + c->cfg.storage * 2 + (h.general ? 1 : 0);
 }
 
-// Steps a group's fused launches take at a time (1: none).
-static int group_fused(const lbm_ctx* c) {
-  if (c->cfg.lattice != LBM_D2Q9 || (c->cfg.flags & (LBM_BGK | LBM_MRT))) return 1;
-  return multi2d_steps(c->cfg.storage, sweep_args(c, 0, 0, 0).general, (uint32_t)c->cfg.nx,
-                       (uint32_t)c->cfg.ny, true);
+// A group is stepped in passes where they are expected to take under this share
+// of the time of single steps.  Beside other groups single steps compete for
+// memory, which passes spare, so there passes are kept unless they are clearly
+// slower.  ms of 64 steps, single / passes: alone, eight FP32 channels of
+// 300 x 280 1.05 / 0.93, one of 300 x 300 0.48 / 0.55, two FP16S ones of 2000 x 1000
+// 2.9 / 4.6; four groups together, 12 jobs of 256 to 2048 cells a side 7.0 / 6.4, of 128
+// to 512 1.17 / 1.04.
+constexpr double kPaysAlone = 0.95, kPaysBeside = 1.5;
+// A job whose pass takes more than this many times its single steps at full
+// load has a grid too narrow for the tiles; it takes single steps in any group
+// (64 steps of eight FP32 channels of 8 x 20000: 1.8 ms, 10.7 in passes).
+constexpr double kNarrow = 2.0;
+
+static bool takes_passes(const lbm_ctx* c, int fused) {
+  if (fused == 1) return false;
+  const bool general = sweep_args(c, 0, 0, 0).general;
+  const uint32_t nx = (uint32_t)c->cfg.nx, ny = (uint32_t)c->cfg.ny;
+  return nx >= 4 && ny >= 4 &&
+         batch2d_time(c->cfg.storage, general, nx, ny).cells <
+             kNarrow * fused * step2d_time(c->cfg.storage, general, true, nx, ny).cells;
+}
+
+// Steps the `count` contexts ctx(0), ctx(1), ... of a group take at a time (1:
+// single steps): the time of passes is that of the jobs that take them and, in
+// launches of their own, of the single steps of the others.
+template <class F>
+static int group_fused(size_t count, bool alone, F&& ctx) {
+  const lbm_ctx* c0 = ctx(0);
+  const bool general = sweep_args(c0, 0, 0, 0).general;
+  if (c0->cfg.lattice != LBM_D2Q9 || (c0->cfg.flags & (LBM_BGK | LBM_MRT))) return 1;
+  const int steps = batch2d_steps(c0->cfg.storage, general);
+  Time2d step{}, pass{};
+  double all = 0, passes = 0, beside = 0;  // cells of single steps, of passes, of the steps beside
+  for (size_t k = 0; k < count; ++k) {
+    const lbm_ctx* c = ctx(k);
+    const uint32_t nx = (uint32_t)c->cfg.nx, ny = (uint32_t)c->cfg.ny;
+    step = step2d_time(c->cfg.storage, general, true, nx, ny);
+    pass = batch2d_time(c->cfg.storage, general, nx, ny);
+    const bool takes = takes_passes(c, steps);
+    all += step.cells;
+    (takes ? passes : beside) += takes ? pass.cells : step.cells;
+  }
+  if (passes == 0) return 1;
+  const double mixed = (pass.launch + passes) / steps + (beside > 0 ? step.launch + beside : 0.0);
+  return mixed < (alone ? kPaysAlone : kPaysBeside) * (step.launch + all) ? steps : 1;
 }
 
 // The batch table entry of a context.
-static void fill_job(BatchJob& J, lbm_ctx* c, int64_t steps, int block, uint32_t tile_begin,
-                     uint32_t ftile_begin) {
+static void fill_job(BatchJob& J, lbm_ctx* c, int64_t steps, int fused, int block,
+                     uint32_t tile_begin, uint32_t ftile_begin) {
   const Level& L = c->lv[0];
   std::memset(&J, 0, sizeof J);
   J.h = sweep_args(c, 0, L.cur, 0);
@@ -181,9 +221,7 @@ static void fill_job(BatchJob& J, lbm_ctx* c, int64_t steps, int block, uint32_t
   J.cur0 = L.cur;
   J.t0 = (uint64_t)L.t;
   J.steps = steps;
-  // (a grid too narrow for the fused tiles takes single steps in any group)
-  const int fused = group_fused(c);
-  if (fused > 1) {
+  if (takes_passes(c, fused)) {
     J.flips0 = steps / fused;
     J.done0 = J.flips0 * fused;
   }
@@ -196,11 +234,9 @@ static void fill_job(BatchJob& J, lbm_ctx* c, int64_t steps, int block, uint32_t
 
 // What the launches of a group cover.
 struct GroupPlan {
-  int fused = 1;           // steps per fused launch
   int64_t fused_launches = 0, single_launches = 0;
   uint32_t tiles = 0, ftiles = 0;
   void add(const lbm_ctx* c, const BatchJob& J) {
-    fused = std::max(fused, group_fused(c));
     fused_launches = std::max(fused_launches, J.flips0);
     single_launches = std::max(single_launches, J.steps - J.done0);
     tiles += J.ntiles;
@@ -215,8 +251,10 @@ static void advance_job(lbm_ctx* c, const BatchJob& J) {
   c->t += J.steps;
 }
 
-// One batch of contexts sharing a kernel variant and workgroup size.
-static int run_group(BatchRunner* r, const std::vector<std::pair<lbm_ctx*, int64_t>>& grp) {
+// One batch of contexts sharing a kernel variant and workgroup size (alone: the
+// only group of the call).
+static int run_group(BatchRunner* r, const std::vector<std::pair<lbm_ctx*, int64_t>>& grp,
+                     bool alone) {
   lbm_ctx* c0 = grp[0].first;
   const int variant = batch_variant(c0);
   const int block = c0->block;
@@ -224,9 +262,10 @@ static int run_group(BatchRunner* r, const std::vector<std::pair<lbm_ctx*, int64
   if (rc != LBM_OK) return rc;
   hipError_t e = hipEventSynchronize(r->staged);
   if (e != hipSuccess) return hip_error(e, "batch staging wait");
+  const int fused = group_fused(grp.size(), alone, [&](size_t k) { return grp[k].first; });
   GroupPlan plan;
   for (size_t k = 0; k < grp.size(); ++k) {
-    fill_job(r->h_jobs[k], grp[k].first, grp[k].second, block, plan.tiles, plan.ftiles);
+    fill_job(r->h_jobs[k], grp[k].first, grp[k].second, fused, block, plan.tiles, plan.ftiles);
     plan.add(grp[k].first, r->h_jobs[k]);
   }
   if (plan.fused_launches + plan.single_launches == 0) return LBM_OK;
@@ -245,18 +284,18 @@ static int run_group(BatchRunner* r, const std::vector<std::pair<lbm_ctx*, int64
   int64_t base = 0;  // the device-side step index, advanced by the graphs
   // `count` launches, index 0 ... count - 1, of the fused or the one-step
   // kernel
-  auto launches = [&](int fused, int64_t count) -> int {
+  auto launches = [&](int per_launch, int64_t count) -> int {
     if (count == 0) return LBM_OK;
-    auto gk = std::make_pair(variant, fused > 1 ? -fused : block);
-    if (!r->grids.count(gk)) r->grids[gk] = batch_grid(variant, fused, block);
+    auto gk = std::make_pair(variant, per_launch > 1 ? -per_launch : block);
+    if (!r->grids.count(gk)) r->grids[gk] = batch_grid(variant, per_launch, block);
     const int grid = r->grids[gk];
     if (grid <= 0) return set_error(LBM_EDEVICE, "batch occupancy query failed");
     int64_t done = 0;
-    const int64_t per = kBatchGraphSteps / fused;
+    const int64_t per = kBatchGraphSteps / per_launch;
     // (a graph counts from the index the device holds)
     if (use_graph && base == 0 && count >= per) {
       GraphEntry* g = nullptr;
-      const int rc2 = graph_for(r, variant, fused, block, grid, &g);
+      const int rc2 = graph_for(r, variant, per_launch, block, grid, &g);
       if (rc2 != LBM_OK) return rc2;
       for (; done + per <= count; done += per) {
         e = hipGraphLaunch(g->exec, r->stream);
@@ -265,13 +304,13 @@ static int run_group(BatchRunner* r, const std::vector<std::pair<lbm_ctx*, int64
       base = done;
     }
     for (; done < count; ++done) {
-      e = launch_batch(variant, fused, r->d_jobs, r->d_hdr, (int32_t)(done - base), block, grid,
-                       r->stream);
+      e = launch_batch(variant, per_launch, r->d_jobs, r->d_hdr, (int32_t)(done - base), block,
+                       grid, r->stream);
       if (e != hipSuccess) return hip_error(e, "batch launch");
     }
     return LBM_OK;
   };
-  rc = launches(plan.fused, plan.fused_launches);
+  rc = launches(fused, plan.fused_launches);
   if (rc == LBM_OK) rc = launches(1, plan.single_launches);
   if (rc != LBM_OK) return rc;
   for (size_t k = 0; k < grp.size(); ++k) advance_job(grp[k].first, r->h_jobs[k]);
@@ -342,10 +381,11 @@ static int run_group_noalloc(lbm_ctx* const* ctxs, const int64_t* steps, const i
   const int variant = batch_variant(c0);
   const int block = c0->block;
   hipStream_t st = c0->stream;
+  const int fused = group_fused((size_t)count, true, [&](size_t k) { return ctxs[order[k]]; });
   GroupPlan plan;
   for (int k = 0; k < count; ++k) {
     BatchJob J;
-    fill_job(J, ctxs[order[k]], steps[order[k]], block, 0, 0);
+    fill_job(J, ctxs[order[k]], steps[order[k]], fused, block, 0, 0);
     plan.add(ctxs[order[k]], J);
   }
   if (plan.fused_launches + plan.single_launches == 0) return LBM_OK;
@@ -356,7 +396,7 @@ static int run_group_noalloc(lbm_ctx* const* ctxs, const int64_t* steps, const i
     chunk.count = (uint32_t)std::min(kTableChunk, count - k0);
     for (uint32_t k = 0; k < chunk.count; ++k) {
       const int j = order[k0 + (int)k];
-      fill_job(chunk.jobs[k], ctxs[j], steps[j], block, tile_begin, ftile_begin);
+      fill_job(chunk.jobs[k], ctxs[j], steps[j], fused, block, tile_begin, ftile_begin);
       tile_begin += chunk.jobs[k].ntiles;
       ftile_begin += multi2d_tiles((uint32_t)ctxs[j]->cfg.nx, (uint32_t)ctxs[j]->cfg.ny);
     }
@@ -371,22 +411,22 @@ static int run_group_noalloc(lbm_ctx* const* ctxs, const int64_t* steps, const i
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_error(e, "allocation-free table upload");
   }
-  auto launches = [&](int fused, int64_t n) -> int {
+  auto launches = [&](int per_launch, int64_t n) -> int {
     if (n == 0) return LBM_OK;
-    const int grid = batch_grid(variant, fused, block);
+    const int grid = batch_grid(variant, per_launch, block);
     if (grid <= 0) return set_error(LBM_EDEVICE, "batch occupancy query failed");
     for (int64_t s = 0; s < n; ++s) {
-      hipError_t e = launch_batch(variant, fused, jobs, hdr, (int32_t)s, block, grid, st);
+      hipError_t e = launch_batch(variant, per_launch, jobs, hdr, (int32_t)s, block, grid, st);
       if (e != hipSuccess) return hip_error(e, "batch launch");
     }
     return LBM_OK;
   };
-  int rc = launches(plan.fused, plan.fused_launches);
+  int rc = launches(fused, plan.fused_launches);
   if (rc == LBM_OK) rc = launches(1, plan.single_launches);
   if (rc != LBM_OK) return rc;
   for (int k = 0; k < count; ++k) {
     BatchJob J;
-    fill_job(J, ctxs[order[k]], steps[order[k]], block, 0, 0);
+    fill_job(J, ctxs[order[k]], steps[order[k]], fused, block, 0, 0);
     advance_job(ctxs[order[k]], J);
   }
   return LBM_OK;
@@ -519,7 +559,7 @@ int lbm_step_batch(lbm_ctx* const* ctxs, const int64_t* steps, int n) {
   for (int k = 0; k < n; ++k)
     groups[std::make_pair(batch_variant(ctxs[k]), ctxs[k]->block)].push_back(
         {ctxs[k], steps[k]});
-  if (groups.size() == 1) return run_group(r, groups.begin()->second);
+  if (groups.size() == 1) return run_group(r, groups.begin()->second, true);
   // groups after the first run concurrently on lanes (one stream each):
   // a small group's launches fill the device poorly on their own
   hipError_t e = hipEventRecord(r->fork, r->stream);
@@ -536,7 +576,7 @@ int lbm_step_batch(lbm_ctx* const* ctxs, const int64_t* steps, int n) {
         break;
       }
     }
-    rc = run_group(x, kv.second);
+    rc = run_group(x, kv.second, false);
     if (g > 0) {
       e = hipEventRecord(x->done, x->stream);
       if (e == hipSuccess) e = hipStreamWaitEvent(r->stream, x->done, 0);
