@@ -30,12 +30,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
-# workgroup size of the one-step sweep of the headline grid (the timed steps
-# are taken two at a time by a kernel whose workgroups are fixed)
+# workgroup size of the one-step sweep of the headline grid (passes of several
+# steps have workgroups of their own)
 HEADLINE_BLOCK = 256
-# steps the library takes per pass over the populations of these grids (even
-# counts): each pass reads and writes every population once
-STEPS_PER_PASS = 2
 METRIC = "MLUPS & % HBM roofline (D3Q19 256³); p50/p99 latency, batched serving"
 # sources each profiled kernel is compiled from
 SOURCES = {"k_sweep": ["kernels.hip", "sweep.hpp", "kernels.hpp", "lattice.hpp"],
@@ -53,6 +50,18 @@ def kernel_hash(kernel="k_sweep"):
         with open(os.path.join(ROOT, "paper_1710_02065_amd", "csrc", s), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
+
+
+def launches(sim, steps):
+    """Kernel launches of step(steps) on an unrefined grid: the library says how
+    many steps it takes per pass, what is left over is counted one by one."""
+    return steps // sim.steps_per_pass + steps % sim.steps_per_pass
+
+
+def lup_bytes(sim, steps, values, size):
+    """Algorithmic bytes per lattice update of step(steps): every launch reads
+    and writes each of a cell's values once."""
+    return 2 * values * size * launches(sim, steps) / steps
 
 
 def measured_traffic(name):
@@ -355,12 +364,14 @@ def other_configs(lbm, torch, steps, shedding_steps,
         sim.block = lbm.lbm_autotune(sim.ctx, 2)
         ms = time_steps(sim, torch, steps)
         N = nx * ny
-        bytes_lup = (2 * 9 * 4 + 1) / STEPS_PER_PASS
+        # 72 B of populations and 1 B of mask per cell and launch
+        bytes_lup = lup_bytes(sim, steps, 9, 4) * 73 / 72
         res["d2q9_cylinder_2048x1024_f32"] = dict(
             mlups=round(N * steps / (ms * 1e3), 1), steps=steps, workgroup=sim.block,
             hbm_gbs=round(bytes_lup * N * steps / (ms / 1e3) / 1e9, 1),
-            note="72 B populations + 1 B mask per cell and pass of two steps; 151 MB of state "
-                 "fits the 256 MB MALL")
+            steps_per_pass=sim.steps_per_pass,
+            note="72 B populations + 1 B mask per cell and pass; 151 MB of state fits the "
+                 "256 MB MALL")
         del sim
         torch.cuda.empty_cache()
         # the channel in FP32 against the FP64 build (equal to the oracle within
@@ -634,13 +645,18 @@ def main():
     sim32, ms32, windows = run_gpu(lbm, torch, hs, n, args.steps, args.warmup, fields, block,
                                    windows=args.windows)
     mlups32 = N * args.steps / (ms32 * 1e3)
-    per_pass = 1 if moment else STEPS_PER_PASS
+    per_pass = sim32.steps_per_pass
+    nlaunch = launches(sim32, args.steps)
     bytes_launch = 2 * (10 if moment else 19) * 4 * N
-    per_launch_s = ms32 / 1e3 / args.steps * per_pass
+    per_launch_s = ms32 / 1e3 / nlaunch
     wg32 = sim32.block
     achieved = bytes_launch / per_launch_s / 1e9
-    kname = "k_msweep_d3q19_m32_256" if moment else "k_pair3d_d3q19_f32_256"
-    traffic = measured_traffic(kname) if n == 256 else None
+    kernel = "k_msweep" if moment else ("k_pair3d" if per_pass > 1 else "k_sweep")
+    # one kernel took every step (an odd count ends in a single sweep)
+    uniform = args.steps % per_pass == 0
+    traffic = None
+    if n == 256 and uniform:
+        traffic = measured_traffic("%s_d3q19_%s_256" % (kernel, hs))
 
     variants = {}
     precision = {}
@@ -651,12 +667,11 @@ def main():
             log("timing %s" % st)
             sv, msv, _ = run_gpu(lbm, torch, st, n, args.steps, args.warmup, fields,
                                  HEADLINE_BLOCK if st == "f32" else 0)
-            # the moment storages move 10 values per cell each way and step,
-            # the others 19 per pass
-            vals = 10 if st.startswith("m") else 19 / STEPS_PER_PASS
-            b = round(2 * vals * lbm.STORAGE_BYTES[lbm.STORAGE[st]])
+            # the moment storages move 10 values per cell each way, the others 19
+            b = lup_bytes(sv, args.steps, 10 if st.startswith("m") else 19,
+                          lbm.STORAGE_BYTES[lbm.STORAGE[st]])
             mv = N * args.steps / (msv * 1e3)
-            variants[st] = dict(value=round(mv, 1), unit="MLUPS", bytes_per_lup=b,
+            variants[st] = dict(value=round(mv, 1), unit="MLUPS", bytes_per_lup=round(b, 1),
                                 hbm_gbs=round(b * N / (msv / 1e3 / args.steps) / 1e9, 1),
                                 speedup_vs_headline=round(mv / mlups32, 3), workgroup=sv.block)
             if st.startswith("m"):
@@ -671,11 +686,11 @@ def main():
                 log("timing d3q27 %s %s" % (st, name))
                 sv, msv, _ = run_gpu(lbm, torch, st, n, max(args.steps // 4, 50),
                                      args.warmup // 4, fields, 0, lattice=27, flags=fl)
-                b = round(2 * (10 if st.startswith("m") else 27 / STEPS_PER_PASS) *
-                          lbm.STORAGE_BYTES[lbm.STORAGE[st]])
                 ns = max(args.steps // 4, 50)
+                b = lup_bytes(sv, ns, 10 if st.startswith("m") else 27,
+                              lbm.STORAGE_BYTES[lbm.STORAGE[st]])
                 order["d3q27_%s_%s" % (st, name)] = dict(
-                    mlups=round(N * ns / (msv * 1e3), 1), bytes_per_lup=b,
+                    mlups=round(N * ns / (msv * 1e3), 1), bytes_per_lup=round(b, 1),
                     hbm_gbs=round(b * N * ns / (msv / 1e3) / 1e9, 1), workgroup=sv.block)
                 del sv
                 torch.cuda.empty_cache()
@@ -710,9 +725,10 @@ def main():
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
             "traffic": traffic,
             "algorithmic_bytes_per_launch": bytes_launch,
-            "steps_per_launch": per_pass,
+            "steps_per_launch": per_pass if uniform else round(args.steps / nlaunch, 3),
             "measured_copy_gbs": copy_gbs,
-            "kernel": "k_msweep<D3Q19, float>" if moment else "k_pair3d<D3Q19, f32>"},
+            "kernel": "%s<D3Q19, %s>%s" % (kernel, "float" if moment else hs,
+                                           "" if uniform else " and one k_sweep")},
     }
     if variants:
         out["variants"] = variants
