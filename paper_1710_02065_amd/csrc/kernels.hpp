@@ -328,12 +328,34 @@ __device__ __forceinline__ void static_for(F&& f) {
 __device__ __forceinline__ float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-// Rest part w_i rho0 of population i, rounded (a statement of its own: the
-// product is not contracted into the sum it enters).
+// The rest part w_i rho0 of population i, added to a x and taken off the sum s
+// of a pair: the two cancel exactly, or mass drifts.  In FP32 on D2Q9 and D3Q19
+// it is rounded, one register per weight kept from the one to the other; D3Q27
+// and FP64 have no registers for that (the batched FP32 sweep of D3Q27 spilled
+// 3.5 KB a lane: 68 us a step for six 64 x 60 x 56 boxes, 1340) and add the
+// product itself, D3Q27 at one multiplication more per population.
+template <class L, class R>
+constexpr bool kRoundedRest = L::Q != 27 && sizeof(R) == 4;
 template <class L, int I, class R>
-__device__ __forceinline__ R rest_part(R rho0) {
-  const R r = (R)L::w(I) * rho0;
-  return r;
+__device__ __forceinline__ R add_rest(R rho0, R a, R x) {
+  constexpr R w = (R)L::w(I);
+  if constexpr (kRoundedRest<L, R>) {
+    const R r = w * rho0;  // (a statement of its own: not contracted into the sum)
+    return fused(a, x, r);
+  } else {
+    const R y = a * x;
+    return fused(w, rho0, y);
+  }
+}
+template <class L, int I, class R>
+__device__ __forceinline__ R take_rest(R rho0, int parts, R s) {
+  constexpr R w = (R)L::w(I);
+  if constexpr (kRoundedRest<L, R>) {
+    const R r = w * rho0;
+    return fused((R)-parts, r, s);
+  } else {
+    return fused((R)-parts * w, rho0, s);
+  }
 }
 
 // All q populations from the coefficients.  Directions come in opposite
@@ -342,7 +364,7 @@ __device__ __forceinline__ R rest_part(R rho0) {
 // costs one even and one odd sum.  Every coefficient is multiplied by the
 // smallest weight first, which leaves the populations of that weight without
 // a multiplication and the others with an exact one (the weights of a
-// lattice differ by powers of two, but for the 1/3 of D3Q19).  The odd
+// lattice differ by powers of two, but for the 1/3 of D3Q19, below).  The odd
 // part is a sum over the axes, 3 xi_a T_a(xi_b^2, xi_c^2), with
 //   T_a = m1_a + (xi_b^2 - cs^2) A_abb / 3 + (xi_c^2 - cs^2) A_acc / 3
 // shared by all directions with the same squares, plus the xyz term where
@@ -351,17 +373,17 @@ __device__ __forceinline__ R rest_part(R rho0) {
 // to every direction.  The factors the terms enter with (1.5, 4.5, 9, 3, and
 // 2/9 against 1/9) are exact or exact multiples of each other, so that mass
 // and momentum are conserved to the rounding of the sums: scaled each by the
-// weight instead (1.5 w, 4.5 w, 3 w rounded apart) they drift.
-// kPlain: the populations themselves, f = h + w rho0, instead of their
-// deviations h.  The rest part is added last, so that every sum before it is
-// of deviations, a hundredth of f, and only the result is rounded at the size
-// of f (kernels started from w (rho0 + m0) round every sum at that size: FP32
-// density and velocity 60 steps on, against FP64, D3Q27 6.4e-5 / 1.4e-6,
-// every order 7.9e-5 / 1.8e-6, D3Q19 3.2e-5 / 9.9e-7).  It is rounded
-// as stored_moments takes it off (rest_part): with the two a rounding apart,
-// D3Q19's mass drifts (p' after 5000 steps of 256^3 5e-2 off the FP64 run).
-template <class L, class R, bool kPlain>
-__device__ __forceinline__ void rebuild_all(const Coeffs<L, R>& c, R rho0, R out[L::Q]) {
+// weight instead (1.5 w, 4.5 w, 3 w rounded apart) they drift.  `base` is
+// added to m0 (rho0 when the stored value is f itself, 0 when it is the
+// deviation from rest).
+// kLast (FP32 populations that store f): the rest part of every population is
+// added last, so that the sums before it are of deviations, a hundredth of f, and
+// only the result is rounded at the size of f.  Error of density / velocity
+// against FP64 after 60 steps, with `base` in the sums / last: D3Q27 3.8e-5 1.4e-6 /
+// 1.5e-5 8.4e-7, every order 4.9e-5 1.8e-6 / 1.5e-5 8.5e-7, D3Q19 2.0e-5 1.0e-6 /
+// 1.2e-5 8.1e-7.  FP64 would pay for it in registers (its D3Q27 sweeps spilled).
+template <class L, class R, bool kLast>
+__device__ __forceinline__ void rebuild_all(const Coeffs<L, R>& c, R base, R out[L::Q]) {
   constexpr double we = L::w(L::Q - 1);
   R m2[6], t1[3];
 #pragma unroll
@@ -369,9 +391,21 @@ __device__ __forceinline__ void rebuild_all(const Coeffs<L, R>& c, R rho0, R out
 #pragma unroll
   for (int a = 0; a < 3; ++a) t1[a] = (R)we * c.m1[a];
   const R tr = m2[0] + m2[1] + (L::D == 3 ? m2[2] : (R)0);
-  // even part at xi = 0: m0 - cs^2 tr / (2 cs^4) = m0 - 1.5 tr
-  const R e0 = (R)we * c.m0 - (R)1.5 * tr;
-  R er = e0;
+  // even part at xi = 0: m0 - cs^2 tr / (2 cs^4) = m0 - 1.5 tr.  D3Q19's rest
+  // weight is 12 times the smallest, and 12 we is not the rounded 1/3 that
+  // stored_moments takes off: with `base` inside that factor every step added
+  // their difference to the mass (FP32 p' after 5000 steps 5e-2 off the FP64 run
+  // at 256^3), so `base` joins the rest population and the others apart.
+  constexpr bool kApart = L::Q != 27;
+  R e0, er;
+  if constexpr (kLast) {
+    e0 = er = (R)we * c.m0 - (R)1.5 * tr;
+  } else if constexpr (kApart) {
+    er = (R)we * c.m0 - (R)1.5 * tr;
+    e0 = (R)we * base + er;
+  } else {
+    e0 = er = (R)we * (base + c.m0) - (R)1.5 * tr;
+  }
   // third-order coefficients A_abb, A_acc over their norms: (xyy, xzz),
   // (xxy, yzz), (xxz, yyz); D3Q19 resolves their sum and difference only
   constexpr int kA[3][2] = {{kXYY, kXZZ}, {kXXY, kYZZ}, {kXXZ, kYYZ}};
@@ -417,16 +451,13 @@ __device__ __forceinline__ void rebuild_all(const Coeffs<L, R>& c, R rho0, R out
     constexpr double hk = high_h<L>(0, decltype(KK)::value);
     if constexpr (hk != 0.0) er += (R)hk * mh[decltype(KK)::value];
   });
-  // population i from its sum over the smallest weight
-  auto put = [&](auto I, R x) {
-    constexpr int i = decltype(I)::value;
-    constexpr R w = (R)(L::w(i) / we);
-    if constexpr (kPlain)
-      return fused(w, x, rest_part<L, i>(rho0));
-    else
-      return w * x;
-  };
-  out[0] = put(std::integral_constant<int, 0>{}, er);
+  if constexpr (!kLast) er = (R)(L::w(0) / we) * er;
+  if constexpr (kLast)
+    out[0] = add_rest<L, 0>(base, (R)(L::w(0) / we), er);
+  else if constexpr (kApart)
+    out[0] = (R)L::w(0) * base + er;
+  else
+    out[0] = er;
   static_for<0, (L::Q - 1) / 2>([&](auto K) {
     constexpr int i = 1 + 2 * decltype(K)::value;
     constexpr Dir v = L::dir(i);
@@ -465,8 +496,14 @@ __device__ __forceinline__ void rebuild_all(const Coeffs<L, R>& c, R rho0, R out
           odd += (R)hk * mh[k];
       }
     });
-    out[i] = put(std::integral_constant<int, i>{}, even + (R)3 * odd);
-    out[i + 1] = put(std::integral_constant<int, i + 1>{}, even - (R)3 * odd);
+    constexpr R w = (R)(L::w(i) / we);
+    if constexpr (kLast) {
+      out[i] = add_rest<L, i>(base, w, even + (R)3 * odd);
+      out[i + 1] = add_rest<L, i>(base, w, even - (R)3 * odd);
+    } else {
+      out[i] = w * (even + (R)3 * odd);
+      out[i + 1] = w * (even - (R)3 * odd);
+    }
   });
 }
 
@@ -641,11 +678,11 @@ __device__ __forceinline__ void stored_moments(const typename S::T raw[L::Q],
     if constexpr (S::kShifted)
       s[k] = a + b;
     else
-      s[k] = fused((R)-2, rest_part<L, 1 + 2 * k>(rho0), a + b);
+      s[k] = take_rest<L, 1 + 2 * k>(rho0, 2, a + b);
     d[k] = a - b;
   });
   R h0 = (R)raw[0];
-  if constexpr (!S::kShifted) h0 -= rest_part<L, 0>(rho0);
+  if constexpr (!S::kShifted) h0 = take_rest<L, 0>(rho0, 1, h0);
   pair_moments<L, R>(h0, s, d, drho, j, P);
 }
 
@@ -747,14 +784,23 @@ __device__ __forceinline__ R collide_coeffs(R drho, R j[3], const R P[6], R omeg
   return rho;
 }
 
-// Collision of one cell: coefficients and rebuild (kPlain: see rebuild_all).
-template <class L, class R, bool kSponge, bool kPlain>
+// Populations from the Hermite coefficients (`base` added to m0: rho0 when
+// the stored value is f itself, 0 when it is the deviation from rest).  kPlain:
+// `base` is rho0 as stored_moments takes it off (not a share of it, as in
+// collide_bgk).
+template <class L, class R, bool kPlain = false>
+__device__ __forceinline__ void rebuild_from(const Coeffs<L, R>& c, R base, R out[L::Q]) {
+  rebuild_all<L, R, kPlain && sizeof(R) == 4>(c, base, out);
+}
+
+// Collision of one cell: coefficients and rebuild.
+template <class L, class R, bool kSponge, bool kPlain = false>
 __device__ __forceinline__ R collide_moments(R drho, R j[3], const R P[6], R omega1, R rho0,
-                                             R chi, R rho_ref, const R uref[3], R out[L::Q],
-                                             CellMoments<R>* mo = nullptr) {
+                                             R chi, R rho_ref, const R uref[3], R base,
+                                             R out[L::Q], CellMoments<R>* mo = nullptr) {
   Coeffs<L, R> c;
   const R rho = collide_coeffs<L, R, kSponge>(drho, j, P, omega1, rho0, chi, rho_ref, uref, c, mo);
-  rebuild_all<L, R, kPlain>(c, rho0, out);
+  rebuild_from<L, R, kPlain>(c, base, out);
   return rho;
 }
 
@@ -766,8 +812,8 @@ __device__ __forceinline__ R collide(const R h[L::Q], R omega1, R rho0, R chi, R
                                      CellMoments<R>* mo = nullptr) {
   R drho, j[3], P[6];
   raw_moments<L, R>(h, drho, j, P);
-  return collide_moments<L, R, kSponge, false>(drho, j, P, omega1, rho0, chi, rho_ref, uref, out,
-                                               mo);
+  return collide_moments<L, R, kSponge>(drho, j, P, omega1, rho0, chi, rho_ref, uref, (R)0,
+                                        out, mo);
 }
 
 // ------------------------------------------------------------------------
@@ -781,7 +827,7 @@ __device__ __forceinline__ R collide(const R h[L::Q], R omega1, R rho0, R chi, R
 // regularized operator:
 //   post = f - (f - feq(rho*, u)) / tau + chi (feq(rho_ref, u_ref) - feq(rho*, u)).
 // The equilibria are rebuilt from their Hermite coefficients (second order
-// only); for the plain formats omega rho0 carries the rest part of
+// only); base = omega rho0 for the plain formats carries the rest part of
 // omega feq + chi (fref - feq).
 template <class L, class S>
 __device__ __forceinline__ typename S::R collide_bgk(const typename S::T raw[L::Q],
@@ -816,7 +862,7 @@ __device__ __forceinline__ typename S::R collide_bgk(const typename S::T raw[L::
   c.m2[5] = e * j[1] * u[2] + chi * ru[1] * uref[2];
 #pragma unroll
   for (int k = 0; k < 7; ++k) c.m3[k] = (R)0;
-  rebuild_all<L, R, !S::kShifted>(c, omega * rho0, post);
+  rebuild_from<L, R>(c, S::kShifted ? (R)0 : omega * rho0, post);
 #pragma unroll
   for (int i = 0; i < L::Q; ++i) post[i] += omega1 * (R)raw[i];
   return rho;
@@ -921,7 +967,7 @@ __device__ __forceinline__ void rebuild_state(R drho, R rho0, const R u[3],
                                               R out[L::Q]) {
   Coeffs<L, R> c;
   state_coeffs<L, R>(drho, rho0, u, a2, omega1, c);
-  rebuild_all<L, R, false>(c, rho0, out);
+  rebuild_from<L, R>(c, (R)0, out);
 }
 
 // ------------------------------------------------------------------------
@@ -944,11 +990,7 @@ __device__ __forceinline__ R sponge_chi(const int32_t* width, R chi_max,
     const R s = (f & 1) ? (R)pos[a] : (R)(n[a] - 1u - pos[a]);
     const R s0 = (R)(int64_t)(n[a] - (uint32_t)W);
     if (s < s0) continue;
-    // (s - s0) / W, correctly rounded, from the width's rounded reciprocal (the
-    // same for every cell) by the remainder step of Markstein, IBM J. Res. Dev.
-    // 34, 111 (1990): the last cells' 1 - d magnifies an error of d by W
-    const R iw = (R)1 / (R)W, q = (s - s0) * iw;
-    const R d = fused(fused(-q, (R)W, s - s0), iw, q);
+    const R d = (s - s0) / (R)W;
     const R sig = (R)(3125.0 / 256.0) * ((R)1 - d) * (d * d) * (d * d);
     best = sig > best ? sig : best;
   }

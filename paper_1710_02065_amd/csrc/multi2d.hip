@@ -359,13 +359,16 @@ static bool small_tiles(int storage, bool general, uint32_t nx, uint32_t ny, uin
 }
 
 // Whether a pass is taken in place of single steps: where it is expected to
-// take under 0.85 of their time, which covers the fit's error (of 366 grids
-// measured four had a pass that was slower, by 2 to 6 %).  us per step, one at a
-// time / in the pass a rule without the times took: periodic 8 x 112500 FP32
-// 14.8 / 33.4, 8 x 3750 FP64 3.1 / 3.6; channel 32 x 28125 FP32 18.2 / 36.1, 96 x 41666 FP64
-// 107 / 118, 130 x 30769 FP16S 51 / 73, 332 x 332 FP64 6.2 / 6.8.
-static bool pays(const Time2d& pass, const Time2d& step, int steps) {
-  return pass.launch + pass.cells < 0.85 * steps * (step.launch + step.cells);
+// take under this share of their time, which balances the fit's errors (of 366
+// grids measured 13 have a pass that is slower, by up to 13 %, and 33 miss one
+// that is faster).  us per step, one at a time / in the pass a rule without the times
+// took: periodic 8 x 112500 FP32 14.8 / 33.4, 8 x 3750 FP64 3.1 / 3.6; channel
+// 32 x 28125 FP32 18.2 / 36.1, 96 x 41666 FP64 107 / 118, 130 x 30769 FP16S 51 / 73,
+// 700 x 500 FP64 13.9 / 9.2.  What is left over by passes of four is two steps at a
+// time only where that is clearly faster.
+constexpr double kPays = 0.89, kTwoPays = 0.85;
+static bool pays(const Time2d& pass, const Time2d& step, int steps, double share) {
+  return pass.launch + pass.cells < share * steps * (step.launch + step.cells);
 }
 
 // Steps per pass of a single grid: four, but two on the general path of the
@@ -380,7 +383,7 @@ int multi2d_steps(int storage, bool general, uint32_t nx, uint32_t ny, uint32_t 
   const int steps = !general || storage == 3 || (uint64_t)nx * ny < (1u << 20) ? 4 : 2;
   const bool small = steps == 4 && small_tiles(storage, general, nx, ny, cus);
   return pays(pass2d_time(storage, general, nx, ny, steps, small),
-              step2d_time(storage, general, false, nx, ny), steps)
+              step2d_time(storage, general, false, nx, ny), steps, kPays)
              ? steps
              : 1;
 }
@@ -389,7 +392,7 @@ int multi2d_steps(int storage, bool general, uint32_t nx, uint32_t ny, uint32_t 
 bool multi2d_two(int storage, bool general, uint32_t nx, uint32_t ny) {
   return nx >= 4 && ny >= 4 &&
          pays(pass2d_time(storage, general, nx, ny, 2, false),
-              step2d_time(storage, general, false, nx, ny), 2);
+              step2d_time(storage, general, false, nx, ny), 2, kTwoPays);
 }
 
 // Steps per pass of a batch: as of a single grid whose tiles fill the device.

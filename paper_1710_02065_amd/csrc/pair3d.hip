@@ -110,8 +110,8 @@ __device__ __forceinline__ typename S::R pair_collide(const typename S::T raw[L:
   R drho, j[3], P[6], post[L::Q];
   const R zero3[3] = {(R)0, (R)0, (R)0};
   stored_moments<L, S>(raw, rho0, drho, j, P);
-  const R rho = collide_moments<L, R, false, !S::kShifted>(drho, j, P, omega1, rho0, (R)0, rho0,
-                                                           zero3, post);
+  const R rho = collide_moments<L, R, false, !S::kShifted>(
+      drho, j, P, omega1, rho0, (R)0, rho0, zero3, S::kShifted ? (R)0 : rho0, post);
 #pragma unroll
   for (int i = 0; i < L::Q; ++i) out[i] = narrow<T>(post[i]);
   return rho;

@@ -361,7 +361,7 @@ __device__ __forceinline__ bool collide_cell(const SweepArgs<S>& a, uint32_t c, 
                                              F&& fixup) {
   using R = typename S::R;
   // the rebuilt values are produced directly in the storage domain
-  constexpr bool kPlain = !S::kShifted;
+  const R base = S::kShifted ? (R)0 : a.rho0;
   R drho, j[3], Pm[6];
   if constexpr (!kGeneral) {
     stored_moments<L, S>(raw, a.rho0, drho, j, Pm);
@@ -370,8 +370,8 @@ __device__ __forceinline__ bool collide_cell(const SweepArgs<S>& a, uint32_t c, 
     else if constexpr (L::kColl == kCollMRT)
       rho = collide_mrt<L, S>(raw, drho, j, a.omega1, a.rho0, post);
     else
-      rho = collide_moments<L, R, false, kPlain>(drho, j, Pm, a.omega1, a.rho0, (R)0, a.rho_ref,
-                                                 a.uref, post);
+      rho = collide_moments<L, R, false, !S::kShifted>(drho, j, Pm, a.omega1, a.rho0, (R)0, a.rho_ref,
+                                         a.uref, base, post);
   } else {
     const uint8_t kind = m & kKindBits;
     if (kind == kSolid || kind >= kCovered) return false;
@@ -421,7 +421,7 @@ __device__ __forceinline__ bool collide_cell(const SweepArgs<S>& a, uint32_t c, 
         if (a.rec || a.recf) record_moments<L, S>(a, mo, x, y, z, c);
       }
     }
-    if (rebuild) rebuild_all<L, R, kPlain>(cf, a.rho0, post);
+    if (rebuild) rebuild_from<L, R, !S::kShifted>(cf, base, post);
   }
   return true;
 }
