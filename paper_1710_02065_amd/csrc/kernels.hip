@@ -18,7 +18,7 @@ namespace hrlbm {
 // the batched sweeps share this code, halo faces included (the batch never
 // has any): one instantiation keeps their results bitwise equal.
 // ------------------------------------------------------------------------
-template <class L, class S, bool kGeneral, bool kNt = false>
+template <class L, class S, bool kGeneral, bool kNt = false, bool kAtOnce = true>
 __device__ __forceinline__ void sweep_cell(const SweepArgs<S>& a, uint32_t c) {
   using R = typename S::R;
   using T = typename S::T;
@@ -62,7 +62,7 @@ __device__ __forceinline__ void sweep_cell(const SweepArgs<S>& a, uint32_t c) {
   }
   auto fixup = [&](T* r) {
     if (m & (kNearFace | kNearSolid))
-      pull_fixup<L, S>(a, x, y, z, c, (m & kNearSolid) != 0, r);
+      pull_fixup<L, S, kAtOnce>(a, x, y, z, c, (m & kNearSolid) != 0, r);
   };
   if (!collide_cell<L, S, kGeneral>(a, c, x, y, z, m, a.t_new, raw, post, rho, fixup)) return;
   // stability watchdog: a rare, benign racy store of 1
@@ -347,8 +347,9 @@ __global__ void k_set_pop(PopArgs a) {
 // memory plus the launch's offset s_off (a captured sequence of launches
 // carries offsets 0, 1, ... and advances the base once at its end), so the
 // sequence replays for any job table.
-// Each cell runs the same sweep_cell instantiation as a solo launch of its
-// context, so results are bitwise those of lbm_step.
+// Each cell runs the sweep_cell of a solo launch of its context (on D3Q27 with
+// the mask bytes of the face rules read one by one), so results are bitwise
+// those of lbm_step.
 // ------------------------------------------------------------------------
 template <class L, class S, bool kGeneral>
 __device__ __forceinline__ void batch_cell(const BatchJob& J, int32_t s, uint32_t c) {
@@ -360,7 +361,7 @@ __device__ __forceinline__ void batch_cell(const BatchJob& J, int32_t s, uint32_
   a.ncell = J.h.nx * J.h.ny * J.h.nz;
   a.div_nx = FastDiv{J.div_nx[0], J.div_nx[1], J.div_nx[2]};
   a.div_ny = FastDiv{J.div_ny[0], J.div_ny[1], J.div_ny[2]};
-  sweep_cell<L, S, kGeneral>(a, c);
+  sweep_cell<L, S, kGeneral, false, L::Q != 27>(a, c);
 }
 
 // Wavefronts per SIMD of the batched sweep: those of the solo sweep, fewer on

@@ -44,12 +44,14 @@ __device__ __forceinline__ int flipped(bool fx, bool fy, bool fz) {
 // (nine at a time) and the reloads are issued without waiting for each other
 // (one mask byte and one reload after the other were up to two memory
 // latencies per direction: D2Q9 300 x 200 channel 6.5 us a step, now 5.5).
-// D3Q27 reads them one by one: its sweep has no registers left for them.
+// kAtOnce = false reads them one by one, for D3Q27 in a batch, whose sweep has no
+// registers left for them (FP32 spilled 2.7 KB a lane; its solo sweep, 200 x 150 x 130
+// with a cylinder: FP32 185 us a step one by one, 173 together, FP16S 169 / 152).
 // Directions that cross no face any lane of the wavefront lies on are passed
 // over by a scalar branch: in an open box most wavefronts hold an end of a row
 // and would spend more on the 26 directions than on the collision.
 // ------------------------------------------------------------------------
-template <class L, class S>
+template <class L, class S, bool kAtOnce = true>
 __device__ __forceinline__ void pull_fixup(const SweepArgs<S>& a, uint32_t x, uint32_t y,
                                            uint32_t z, uint32_t c, bool near_solid,
                                            typename S::T raw[L::Q]) {
@@ -76,7 +78,6 @@ __device__ __forceinline__ void pull_fixup(const SweepArgs<S>& a, uint32_t x, ui
     on[ax][1] = a.face[2 * ax + 1] != kPeriodic && any_lane(pos[ax] + 1 == dims[ax]);
   }
   const bool any_solid = any_lane(near_solid);
-  constexpr bool kAtOnce = L::Q != 27;
   uint32_t solid = 0;  // bit i: the source of population i is SOLID
   if (kAtOnce && near_solid) {
     constexpr int kBatch = 9;
