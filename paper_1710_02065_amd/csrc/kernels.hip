@@ -121,7 +121,8 @@ __global__ void __launch_bounds__(1024)
 
 // ------------------------------------------------------------------------
 // Initial state: f* = f^{eqH}(rho, u) + (1 - 1/tau) f^{neqH}(pi_neq, u),
-// written to both population buffers.
+// written to the current population buffer and, where cells may stay unswept,
+// to the other one.
 // ------------------------------------------------------------------------
 template <class L, class S>
 __global__ void k_init(InitArgs a) {
@@ -483,6 +484,10 @@ __global__ void k_tiles(FlagsArgs a) {
   a.tiles[t] = plain;
 }
 
+// Workgroup of the kernels with one thread per cell or list entry: few items go
+// in workgroups of one wavefront, spread over more CUs.
+static uint32_t list_block(uint32_t n) { return n < (1u << 16) ? 64u : 256u; }
+
 // Halo faces outside the sweep (after initialisation or an import of
 // populations): the face planes' leaving populations into the send
 // buffers, as the sweep packs them, and, with `entering`, the same planes'
@@ -512,14 +517,17 @@ __global__ void k_halo_pack(HaloArgs h) {
   }
 }
 
+// workgroups of the size k_init had, so that a face plane is read on the XCD
+// whose L2 it was just written to
 template <class L>
 static void halo_pack_l(int storage, const HaloArgs& a, hipStream_t st) {
-  const uint32_t blocks = (a.hplane + 255) / 256;
+  const uint32_t size = list_block(a.nx * a.ny * a.nz);
+  const dim3 blocks((a.hplane + size - 1) / size), block(size);
   switch (storage) {
-    case 0: hipLaunchKernelGGL((k_halo_pack<L, StoreF64>), dim3(blocks), dim3(256), 0, st, a); break;
-    case 1: hipLaunchKernelGGL((k_halo_pack<L, StoreF32>), dim3(blocks), dim3(256), 0, st, a); break;
-    case 2: hipLaunchKernelGGL((k_halo_pack<L, StoreF32S>), dim3(blocks), dim3(256), 0, st, a); break;
-    case 3: hipLaunchKernelGGL((k_halo_pack<L, StoreF16S>), dim3(blocks), dim3(256), 0, st, a); break;
+    case 0: hipLaunchKernelGGL((k_halo_pack<L, StoreF64>), blocks, block, 0, st, a); break;
+    case 1: hipLaunchKernelGGL((k_halo_pack<L, StoreF32>), blocks, block, 0, st, a); break;
+    case 2: hipLaunchKernelGGL((k_halo_pack<L, StoreF32S>), blocks, block, 0, st, a); break;
+    case 3: hipLaunchKernelGGL((k_halo_pack<L, StoreF16S>), blocks, block, 0, st, a); break;
   }
 }
 
@@ -711,8 +719,7 @@ hipError_t launch_sweep(int lattice, int storage, const SweepHost& h, int block,
 #define HRLBM_DISPATCH(NAME, ARGS, FULL)                                      \
   template <class L, class S>                                                 \
   static void NAME##_t(const ARGS& a, uint32_t n, hipStream_t st) {           \
-    /* few items: workgroups of one wavefront, spread over more CUs */         \
-    const uint32_t size = n < (1u << 16) ? 64u : 256u;                        \
+    const uint32_t size = list_block(n);                                      \
     const uint32_t blocks = (n + size - 1) / size;                            \
     if (blocks) hipLaunchKernelGGL((k_##NAME<L, S>), dim3(blocks), dim3(size), 0, st, a); \
   }                                                                           \
