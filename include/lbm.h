@@ -171,9 +171,12 @@ typedef struct lbm_config {
   void* stream;          /* hipStream_t for all work; NULL = null stream */
   uint32_t flags;        /* LBM_ALLOW_HIGH_MA | LBM_NO_GRAPH | LBM_FULL_ORDER |
                             LBM_SPONGE_FIELD | LBM_BGK | LBM_MRT */
-  uint32_t block;        /* threads per workgroup for the sweep; 0 = tuned.
-                            Moment storages: planes one workgroup marches
-                            through = block / 16 (4 .. 64) */
+  uint32_t block;        /* threads per workgroup for the one-step sweep; 0 =
+                            tuned.  Passes of several steps have workgroups
+                            of their own (lbm_steps_per_pass): there it
+                            applies to the steps they leave over.  Moment
+                            storages: planes one workgroup marches through =
+                            block / 16 (4 .. 64) */
   int32_t nest_count;    /* further nested boxes, 0 .. LBM_MAX_LEVELS - 2
                             (needs refine_lo/hi) */
   int32_t nest_reserved; /* 0 */
@@ -349,8 +352,9 @@ int lbm_set_interface(lbm_ctx* ctx, int level, const void* in);
 /* Serving: advance ctxs[k] by steps[k] coarse steps, k < n, sharing
  * launches between contexts: the contexts are grouped by lattice, storage,
  * sweep path (fully periodic or not) and workgroup size, and each group
- * advances through persistent launches, each of one step (D2Q9: of two or
- * four, then single ones).  The first group runs
+ * advances through persistent launches, each of one step (D2Q9, where it is
+ * faster: of two or four, which do not depend on the workgroup size, then
+ * single ones).  The first group runs
  * on the contexts' stream, the others concurrently on streams the library
  * owns, ordered after and joined back into the contexts' stream with
  * events, so work queued on that stream before the call precedes every
@@ -382,11 +386,12 @@ int lbm_step_batch(lbm_ctx* const* ctxs, const int64_t* steps, int n);
  * one device (other streams or threads) race. */
 int lbm_step_batch_noalloc(lbm_ctx* const* ctxs, const int64_t* steps, int n);
 
-/* Time the sweep for each candidate workgroup size (64, 128, 256, 512,
- * 1024; for the moment storages the same values select block / 16 planes
- * per workgroup) on this context's current state (the state is restored
- * afterwards), keep the fastest, and return it (> 0) or a negative
- * status. */
+/* Time the one-step sweep for each candidate workgroup size (64, 128, 256,
+ * 512, 1024; for the moment storages the same values select block / 16
+ * planes per workgroup) on this context's current state (the state is
+ * restored afterwards), keep the fastest, and return it (> 0) or a negative
+ * status.  Where lbm_step takes several steps in one pass
+ * (lbm_steps_per_pass > 1) the passes do not depend on it. */
 int lbm_autotune(lbm_ctx* ctx, int trials);
 
 /* Slab decomposition (face rule LBM_HALO; the streaming step of eq.
