@@ -485,7 +485,8 @@ __global__ void k_tiles(FlagsArgs a) {
 
 // Workgroup of the kernels with one thread per cell or list entry: few items go
 // in workgroups of one wavefront, spread over more CUs.
-static uint32_t list_block(uint32_t n) { return n < (1u << 16) ? 64u : 256u; }
+constexpr uint32_t kShortList = 1u << 16;
+static uint32_t list_block(uint32_t n) { return n < kShortList ? 64u : 256u; }
 
 // Halo faces outside the sweep (after initialisation or an import of
 // populations): the face planes' leaving populations into the send
@@ -617,6 +618,31 @@ __global__ void k_ring(RingArgs a) {
   for (int i = 0; i < L::Q; ++i) dst[(uint64_t)i * a.pstride + cf] = vals[i];
 }
 
+// Filtered stress of an IMPORT node's 3^D child neighbours around kc.  In a short
+// list (kTogether) the loads of all neighbours are in flight together: plane after
+// plane they wait for each other.  A long list hides that wait behind other nodes
+// and pays for the registers.  D3Q27 FP32, us, plane by plane / together: 22000
+// nodes 11.8 / 10.9, 46000 18.0 / 17.4, 94000 35.5 / 39.6.
+template <class L, class R, bool kTogether>
+__device__ __forceinline__ void import_filter(const R* M, const ImportArgs& ia,
+                                              const int32_t kc[3], R acc[6]) {
+  constexpr int oz = L::D == 3 ? 1 : 0;
+  constexpr int kPlanes = kTogether ? 2 * oz + 1 : 1;
+  const R w1[3] = {(R)0.25, (R)0.5, (R)0.25};
+#pragma unroll kPlanes
+  for (int o2 = -oz; o2 <= oz; ++o2)
+#pragma unroll
+    for (int o1 = -1; o1 <= 1; ++o1)
+#pragma unroll
+      for (int o0 = -1; o0 <= 1; ++o0) {
+        const uint64_t c = ((uint64_t)(kc[2] + o2) * ia.fny + (uint64_t)(kc[1] + o1)) * ia.fnx +
+                           (uint64_t)(kc[0] + o0);
+        const R w = w1[o0 + 1] * w1[o1 + 1] * (oz ? w1[o2 + 1] : (R)1);
+#pragma unroll
+        for (int q = 0; q < 6; ++q) acc[q] += w * M[c * 10 + 4 + q];
+      }
+}
+
 // IMPORT node state (eq. couplingCF): rho, u of the coincident child node
 // and the (1/4, 1/2, 1/4)-filtered Pi_neq of its 3^D child neighbours, all
 // pre-collision moments of the child at the common time, recorded by the
@@ -634,24 +660,11 @@ __global__ void k_import(ImportArgs ia) {
   int32_t kc[3];
   for (int ax = 0; ax < 3; ++ax) kc[ax] = ax < L::D ? 2 * (p[ax] - ia.lo[ax]) : 0;
   const R* M = (const R*)ia.recf;
-  const R w1[3] = {(R)0.25, (R)0.5, (R)0.25};
-  // unrolled, so that the loads of a node's neighbours are in flight together
-  // (in a loop they waited for each other: 14 us for the shell of a
-  // 89 x 51 x 51 box on D3Q27 FP32, 11 us unrolled)
-  constexpr int oz = L::D == 3 ? 1 : 0;
   R acc[6] = {(R)0, (R)0, (R)0, (R)0, (R)0, (R)0};
-#pragma unroll
-  for (int o2 = -oz; o2 <= oz; ++o2)
-#pragma unroll
-    for (int o1 = -1; o1 <= 1; ++o1)
-#pragma unroll
-      for (int o0 = -1; o0 <= 1; ++o0) {
-        const uint64_t c = ((uint64_t)(kc[2] + o2) * ia.fny + (uint64_t)(kc[1] + o1)) * ia.fnx +
-                           (uint64_t)(kc[0] + o0);
-        const R w = w1[o0 + 1] * w1[o1 + 1] * (oz ? w1[o2 + 1] : (R)1);
-#pragma unroll
-        for (int q = 0; q < 6; ++q) acc[q] += w * M[c * 10 + 4 + q];
-      }
+  if (ia.n < kShortList)
+    import_filter<L, R, true>(M, ia, kc, acc);
+  else
+    import_filter<L, R, false>(M, ia, kc, acc);
   const uint64_t c0 = ((uint64_t)kc[2] * ia.fny + (uint64_t)kc[1]) * ia.fnx + (uint64_t)kc[0];
   const R drho_c = M[c0 * 10];
   const R u_c[3] = {M[c0 * 10 + 1], M[c0 * 10 + 2], L::D == 3 ? M[c0 * 10 + 3] : (R)0};
