@@ -81,7 +81,7 @@ __device__ __forceinline__ void sweep_cell(const SweepArgs<S>& a, uint32_t c) {
 // formats (the HBM stream needs them; without the hint the general path's
 // scalar registers alone would limit it to 7), except the D3Q27 general
 // path, whose 27 pulled values need more than the 64 registers 8 waves
-// leave (68: it runs at 7 waves, asked for 6, which leaves it scalar
+// leave (69: it runs at 7 waves, asked for 6, which leaves it scalar
 // registers too: 1 % faster on a refined jet), and the D3Q27 comparator
 // collisions on either path, which keep the 27 pulled values alive through
 // the rebuild (7 waves: with 64 registers the LBM-BGK sweep spilled 3.5 KB per

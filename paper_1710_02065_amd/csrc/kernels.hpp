@@ -89,7 +89,8 @@ struct StoreF16S {
 // Rounding of a rebuilt value to the storage type.  For binary16 the FP32
 // value is made opaque first: folded into the multiply before it (one mixed
 // instruction, one rounding) the result would depend on how each kernel is
-// compiled.
+// compiled.  That multiply is by a power of two, exact, for every population but
+// D3Q19's rest population, so no other value is rounded twice after its sum.
 template <class T, class R>
 __device__ __forceinline__ T narrow(R v) {
   if constexpr (sizeof(T) == 2) asm("" : "+v"(v));

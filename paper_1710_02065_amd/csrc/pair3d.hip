@@ -7,15 +7,19 @@
 // the one-step sweep would store), puts what streams into the output plane
 // into LDS, and (2) pulls every interior cell's populations from there,
 // collides again and stores the state at t + 2.  The state at t + 1 never
-// reaches HBM: two steps read (1 + 2/TY) q and write q values per cell
-// instead of 2 q + 2 q.  A halo cell's first step is computed by the
-// neighbouring tile too, and its reads find the neighbour's lines in L2.
+// reaches HBM: two steps write q values per cell and read q, where single steps
+// take 2 q + 2 q.  A halo cell's first step is computed by the neighbouring tile
+// too: a workgroup asks for (1 + 2/TX)(1 + 2/TY) = 1.29 times its tile's cells, and
+// the L2 of the XCD that walks its neighbours serves most of the rest (256^3 D3Q19
+// FP32: 1.056 reads of the state reach HBM, 78.1 B per update).
 //
-// Measured on 256^3, one step / two at a time, us per step: D3Q19 FP32 439 /
-// 252 (66.6k MLUPS; of its 660 + 512 populations' traffic per 1024 updates
-// 5.8 TB/s, so HBM still bounds it), FP16S 225 / 175 (bound by its
-// arithmetic: 8 x 390 + 3 x 185 vector instructions per plane of a tile),
-// FP64 928 / 508; D3Q27 FP32 642 / 365, FP16S 315 / 254, FP64 1317 / 768.
+// Measured on 256^3, one step / two at a time, us per step: D3Q19 FP32 445 /
+// 254 (66k MLUPS), FP16S 219 / 173, FP64 915 / 512; D3Q27 FP32 646 / 366, FP16S
+// 317 / 254, FP64 1309 / 779; every order FP32 638 / 392, FP16S 317 / 305, FP64
+// 1321 / 1102.  D3Q19 FP32 is bound by HBM latency: 5.15 TB/s, with two
+// workgroups per CU and two barriers a plane; its vector instructions, at four
+// cycles each and 2.4 GHz, fill 43 % of the time.  FP16S moves 3.8 TB/s and is
+// bound by those more than by HBM: 4280 of them per plane of a tile, 68 %.
 // Tried on the way: populations waiting for their plane in registers instead
 // of LDS (103 vector registers, one workgroup less per CU), 4, 6, 7 and 12
 // rows per tile (266, 338, 311, 287 us at their best chunk length against
@@ -392,11 +396,11 @@ static double iteration_us(int q, int storage) {
 // ceil(workgroups / slots) (zc + 2).  The pass is taken when that many
 // iterations cost less than two sweeps at their 5.5 TB/s and 1.7 us a launch
 // (4.2 us at least).  Both sides measured, us per step, one-step / pass:
-// D3Q19 FP32 256^3 439 / 253, 250 x 131 x 97 87 / 72, 64^3 8.5 / 7,
-// 128 x 64 x 24 6 / 7, 12 x 200 x 64 8 / 14 (lanes of narrow rows idle);
-// FP16S 256^3 225 / 175, 250 x 131 x 97 47 / 36, 200 x 150 x 130 56 / 67
+// D3Q19 FP32 256^3 445 / 254, 250 x 131 x 97 87 / 70, 200 x 150 x 130 105 / 101,
+// 64^3 8.6 / 6.2, 128 x 64 x 24 6 / 7, 12 x 200 x 64 8 / 14 (lanes of narrow rows
+// idle); FP16S 256^3 219 / 173, 250 x 131 x 97 46 / 31, 200 x 150 x 130 55 / 67
 // (a quarter of the lanes idle, and the 2-byte pass is bound by its
-// arithmetic); D3Q27 FP32 256^3 642 / 365; FP64 256^3 D3Q19 928 / 508.
+// arithmetic); D3Q27 FP32 256^3 646 / 366; FP64 256^3 D3Q19 915 / 512.
 // The search takes the rounds r in which a CU works off its workgroups, and the
 // most chunks that fit them; r rounds take at least 2 r iterations more than
 // the cells alone, which ends it after few (10^6 planes of 4 x 4 cells: two).

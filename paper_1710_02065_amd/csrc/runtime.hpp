@@ -47,8 +47,8 @@ struct GraphEntry {
 };
 
 // Steps of level 0 taken in one pass (1: one-step sweeps), in a pass of what is
-// left over (2 or 1), and the planes per workgroup of the 3D pass.  Fixed by the grid and its mask: chosen once, when
-// the grid is initialised.
+// left over (2 or 1), and the planes per workgroup of the 3D pass.  Fixed by the
+// grid and its mask: chosen once, when the grid is initialised.
 struct Fused {
   int steps = 1, rest = 1;
   uint32_t zc = 0;
