@@ -16,9 +16,11 @@ namespace hrlbm {
 // kGeneral = false: every face periodic (or a halo face of the last axis),
 // no mask, no sponge.  The solo and
 // the batched sweeps share this code, halo faces included (the batch never
-// has any): one instantiation keeps their results bitwise equal.
+// has any), so that their results are bitwise equal.  kRingCells = false: no RING
+// cells (a batch is never refined).
 // ------------------------------------------------------------------------
-template <class L, class S, bool kGeneral, bool kNt = false, bool kAtOnce = true>
+template <class L, class S, bool kGeneral, bool kNt = false, bool kAtOnce = true,
+          bool kRingCells = kGeneral>
 __device__ __forceinline__ void sweep_cell(const SweepArgs<S>& a, uint32_t c) {
   using R = typename S::R;
   using T = typename S::T;
@@ -43,7 +45,7 @@ __device__ __forceinline__ void sweep_cell(const SweepArgs<S>& a, uint32_t c) {
     const bool plain = a.tiles && a.tiles[tile];
     if (!plain) m = a.mask ? a.mask[c] : kFluid;  // (every level on this path carries a mask)
     pull_periodic<L, S, kNt>(a, c, x, y, z, raw);
-    ring = (m & kKindBits) == kRing && a.ring_Ma;
+    if constexpr (kRingCells) ring = (m & kKindBits) == kRing && a.ring_Ma;
   }
   if (ring) {
     // a RING node of this (child) level: the coarse-to-fine fill for the
@@ -361,17 +363,18 @@ __device__ __forceinline__ void batch_cell(const BatchJob& J, int32_t s, uint32_
   a.ncell = J.h.nx * J.h.ny * J.h.nz;
   a.div_nx = FastDiv{J.div_nx[0], J.div_nx[1], J.div_nx[2]};
   a.div_ny = FastDiv{J.div_ny[0], J.div_ny[1], J.div_ny[2]};
-  sweep_cell<L, S, kGeneral, false, L::Q != 27>(a, c);
+  sweep_cell<L, S, kGeneral, false, L::Q != 27, false>(a, c);
 }
 
-// Wavefronts per SIMD of the batched sweep: those of the solo sweep, fewer on
-// the 3D general path, where the job lookup's registers on top of the
-// sweep's made 8 (D3Q19) and 7 (D3Q27) waves spill.
+// Wavefronts per SIMD of the batched sweep: those of the solo sweep, fewer in
+// 3D where the job lookup's registers on top of the sweep's made 8 (D3Q19
+// general, D3Q27 periodic) and 7 (D3Q27 general) waves spill.
 template <class L, class S, bool kGeneral>
 struct BatchWaves {
   static constexpr int value =
-      L::D == 3 && kGeneral && sizeof(typename S::T) < 8 ? (L::Q == 27 ? 6 : 7)
-                                                         : SweepWaves<L, S, kGeneral>::value;
+      L::D == 3 && sizeof(typename S::T) < 8 && (kGeneral || L::Q == 27)
+          ? (kGeneral && L::Q == 27 ? 6 : 7)
+          : SweepWaves<L, S, kGeneral>::value;
 };
 
 // One kernel per (lattice, storage, path): the contexts of a batch are

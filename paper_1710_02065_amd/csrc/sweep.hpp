@@ -311,8 +311,13 @@ __device__ __forceinline__ void ring_node(const typename S::R* Ma, const typenam
   const AxisPoints p2 = L::D == 3 ? axis_points(lo[2], k[2]) : AxisPoints{rec_off[2], 1};
   R m[10];
   for (int q = 0; q < 10; ++q) m[q] = (R)0;
+  // (unrolled, the points' loads would take registers from every cell's sweep:
+  // D2Q9 FP64 122 instead of 73)
+#pragma unroll 1
   for (int i2 = 0; i2 < p2.n; ++i2)
+#pragma unroll 1
     for (int i1 = 0; i1 < p1.n; ++i1)
+#pragma unroll 1
       for (int i0 = 0; i0 < p0.n; ++i0) {
         const uint64_t r = ((uint64_t)(p2.first + i2 - rec_off[2]) * rec_dim[1] +
                             (uint64_t)(p1.first + i1 - rec_off[1])) * rec_dim[0] +
