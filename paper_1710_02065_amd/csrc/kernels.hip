@@ -368,12 +368,13 @@ __device__ __forceinline__ void batch_cell(const BatchJob& J, int32_t s, uint32_
 
 // Wavefronts per SIMD of the batched sweep: those of the solo sweep, fewer in
 // 3D where the job lookup's registers on top of the sweep's made 8 (D3Q19
-// general, D3Q27 periodic) and 7 (D3Q27 general) waves spill.
+// general, D3Q27 periodic) and 7 (D3Q27 general; D3Q19 LBM-BGK general in FP32,
+// 2.5 KB a lane) waves spill.
 template <class L, class S, bool kGeneral>
 struct BatchWaves {
   static constexpr int value =
       L::D == 3 && sizeof(typename S::T) < 8 && (kGeneral || L::Q == 27)
-          ? (kGeneral && L::Q == 27 ? 6 : 7)
+          ? (kGeneral && (L::Q == 27 || (L::kColl != kCollRR && sizeof(typename S::T) == 4)) ? 6 : 7)
           : SweepWaves<L, S, kGeneral>::value;
 };
 
